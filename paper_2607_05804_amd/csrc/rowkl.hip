@@ -28,6 +28,11 @@
 // partial sums, stores), and the bf16 kernel comes in two load orders, one
 // of which each call runs (both explained where they are set).
 //
+// Rows that are no whole packs or do not start on one take the same kernel in
+// another form (RowForm), compiled in rowkl_ragged.hip; its bound is the same,
+// HBM, at 5.5 TB/s for 6,000 bf16 rows of 50,257 elements (2.0 TB/s with one
+// element per load) and 5.85 TB/s for 3,000 fp32 rows.
+//
 // Tasks are handed out by an atomic ticket in row-major order, so a
 // workgroup only ever waits for tasks that running workgroups already hold
 // or that the next free workgroup will take; the wait is bounded and reports
@@ -185,6 +190,13 @@ struct Pack<false, 1> {  // one fp32
   }
 };
 
+// one gradient element, as a pack of one element stores it
+template <bool kBf16>
+__device__ inline void store_one(__amdgpu_buffer_rsrc_t r, int off, float g, unsigned flip) {
+  const float x[1] = {g};
+  Pack<kBf16, 1>::store(r, off, 0, Pack<kBf16, 1>::encode(x, flip));
+}
+
 __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Take a ticket: an atomic increment, which the compiler issues as one plain
@@ -294,14 +306,43 @@ __device__ inline void merge_chunk(bool offset, const float* w, float rs, float 
   r.st = fmaf(w[4], ft, r.st);
 }
 
+// Ragged rows (RowForm): where the pack of elements [e, e + kEpv) is read and
+// written (`last`: the row's last whole pack), which of the elements there are
+// its own when that is `shift` elements before e, and an all-ones mask for one.
+__device__ inline int inside_row(int e, int last) { return e < 0 ? 0 : (e > last ? last : e); }
+template <int kEpv>
+__device__ inline unsigned own_bits(int shift) {
+  constexpr unsigned kAll = (1u << kEpv) - 1u;
+  const int s = shift < -kEpv ? -kEpv : (shift > kEpv ? kEpv : shift);
+  return (s >= 0 ? kAll << s : kAll >> -s) & kAll;
+}
+__device__ inline unsigned own_mask(unsigned bits, int j) {
+  return (unsigned)((int)(bits << (31 - j)) >> 31);
+}
+
+// How a row's packs lie.
+//  kAligned: every row is whole packs and starts on one.
+//  kRagged:  rows of any length (>= one pack) and start.  The packs lie on the
+//            grid of the written matrix's cache lines, so that whole-wave
+//            accesses cover whole lines (the same kernel with its packs
+//            counted from each row's first element takes 317 instead of 277 us
+//            for 6,000 bf16 rows of 50,257); the row's first and last packs
+//            are moved inside the row where they would stick out, and the
+//            elements they then share with their neighbours are left out of
+//            the sums.  The shared elements of a gradient row are written
+//            twice, with the same bits.
+//  kScalar:  one element per pack (rows shorter than a 16-byte pack).
+enum RowForm { kAligned, kRagged, kScalar };
+
 // One (row, chunk) task per iteration.  A chunk is the pack range
 // [pack_lo, pack_hi) of the row; thread tid owns packs pack_lo + v * 256 + tid
 // for v < kVpt.  The host's tiling makes every chunk at least 256 (kVpt - 1)
 // packs long, so every pack v < kVpt - 1 lies inside the chunk and only the
-// last one is predicated (kCheckAll: all of them, for the unaligned scalar
-// path, whose chunks carry no such guarantee).
-template <bool kBf16, int kEpv, int kVpt, bool kCheckAll, bool kSplit>
+// last one is predicated (kScalar: all of them; kRagged: the first and the
+// last one, which may stick out of the row).
+template <bool kBf16, int kEpv, int kVpt, RowForm kForm, bool kSplit>
 __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
+  constexpr bool kCheckAll = kForm == kScalar;
   using P = Pack<kBf16, kEpv>;
   constexpr int kEs = kBf16 ? 2 : 4;
   constexpr int kPackBytes = kEpv * kEs;
@@ -366,14 +407,48 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     const long long row = (long long)(task / (unsigned)p.n_chunks);
     const int c = (int)(task - (unsigned)row * (unsigned)p.n_chunks);
     const int pack_lo = __builtin_amdgcn_readfirstlane(s_lo[c]);
-    const int n_valid = __builtin_amdgcn_readfirstlane(s_lo[c + 1]) - pack_lo;  // packs in this chunk
-    const long long col = (long long)pack_lo * kEpv;  // first element of the chunk
+    int pack_hi = __builtin_amdgcn_readfirstlane(s_lo[c + 1]);
+    long long col = (long long)pack_lo * kEpv;  // first element of the chunk
     const int lane_off = tid * kPackBytes;
+    // Ragged rows: the row's first pack begins pre / kEs elements before the
+    // row, on the line that holds the row's first element; a pack that sticks
+    // out of the row is moved inside it by `shift` elements, and its element j
+    // belongs to it only where 0 <= j - shift < kEpv (nowhere, for a pack
+    // wholly outside).  Bit j of edge_bits says so for the thread's first and
+    // last pack: a mask without branches, which the sums' register budget needs.
+    unsigned bits_first = 0, bits_last = 0;
+    int off_first = 0, off_last = 0;  // byte offsets of those packs from the chunk's first element
+    if constexpr (kForm == kRagged) {
+      const char* rows = static_cast<const char*>(p.grad ? p.grad : p.zs);
+      const int pre = (int)(reinterpret_cast<uintptr_t>(rows + row * (p.grad ? p.ld_g : p.ld_s) * kEs) &
+                            (uintptr_t)p.line_mask);
+      const int n_row = (pre + p.vocab * kEs + kPackBytes - 1) / kPackBytes;
+      pack_hi = pack_hi < n_row ? pack_hi : n_row;
+      col -= pre / kEs;
+      const int n = pack_hi - pack_lo;
+      const int e_first = (int)col + tid * kEpv;
+      const int e_last = e_first + (kVpt - 1) * kRowThreads * kEpv;
+      const int at_first = inside_row(e_first, p.vocab - kEpv);
+      const int at_last = inside_row(e_last, p.vocab - kEpv);
+      bits_first = tid < n ? own_bits<kEpv>(e_first - at_first) : 0u;
+      bits_last = (kVpt - 1) * kRowThreads + tid < n ? own_bits<kEpv>(e_last - at_last) : 0u;
+      off_first = (at_first - (int)col) * kEs;
+      off_last = (at_last - (int)col) * kEs;
+    }
+    const int n_valid = pack_hi - pack_lo;  // packs in this chunk
 
     bool valid[kVpt];
 #pragma unroll
-    for (int v = 0; v < kVpt; ++v)
-      valid[v] = (kCheckAll || v == kVpt - 1) ? (v * kRowThreads + tid < n_valid) : true;
+    for (int v = 0; v < kVpt; ++v) {
+      if (kForm == kRagged)
+        valid[v] = v == 0 ? bits_first != 0u : (v == kVpt - 1 ? bits_last != 0u : true);
+      else
+        valid[v] = (kCheckAll || v == kVpt - 1) ? (v * kRowThreads + tid < n_valid) : true;
+    }
+    // the offsets of pack v's loads and stores: per-lane part and uniform part
+#define TURNKL_EDGE(v) (kForm == kRagged && ((v) == 0 || (v) == kVpt - 1))
+#define TURNKL_OFF_V(v) (TURNKL_EDGE(v) ? ((v) == 0 ? off_first : off_last) : lane_off)
+#define TURNKL_OFF_S(v) (TURNKL_EDGE(v) ? 0 : (v) * kStep)
 
     if (!p.mask[row]) {
       if (p.lse && c == 0 && tid == 0) {  // the row is not read: no log-partition function
@@ -386,7 +461,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         const auto rg = chunk_rsrc(static_cast<char*>(p.grad) + (row * p.ld_g + col) * kEs);
 #pragma unroll
         for (int v = 0; v < kVpt; ++v)
-          if (valid[v]) P::store(rg, lane_off, v * kStep, z);
+          if (valid[v]) P::store(rg, TURNKL_OFF_V(v), TURNKL_OFF_S(v), z);
         __builtin_amdgcn_s_setprio(0);
         if (tid == 0) next_task = take_ticket(&p.hdr->ticket);
         // the zeros sit in registers the loop's phi copies may take over
@@ -418,23 +493,23 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     if constexpr (kSplit) {
 #pragma unroll
       for (int v = 0; v < kVpt; ++v) {
-        const bool sure = !kCheckAll && v < kVpt - 1;
-        xs[v].load(rs, sure ? lane_off : (valid[v] ? lane_off : 0),
-                   sure ? v * kStep : (valid[v] ? v * kStep : 0));
+        const bool sure = kForm == kRagged || (!kCheckAll && v < kVpt - 1);
+        xs[v].load(rs, sure ? TURNKL_OFF_V(v) : (valid[v] ? lane_off : 0),
+                   sure ? TURNKL_OFF_S(v) : (valid[v] ? v * kStep : 0));
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int v = 0; v < kVpt; ++v) {
-        const bool sure = !kCheckAll && v < kVpt - 1;
-        xt[v].load(rt, sure ? lane_off : (valid[v] ? lane_off : 0),
-                   sure ? v * kStep : (valid[v] ? v * kStep : 0));
+        const bool sure = kForm == kRagged || (!kCheckAll && v < kVpt - 1);
+        xt[v].load(rt, sure ? TURNKL_OFF_V(v) : (valid[v] ? lane_off : 0),
+                   sure ? TURNKL_OFF_S(v) : (valid[v] ? v * kStep : 0));
       }
     } else {
 #pragma unroll
       for (int v = 0; v < kVpt; ++v) {
-        const bool sure = !kCheckAll && v < kVpt - 1;
-        const int vo = sure ? lane_off : (valid[v] ? lane_off : 0);
-        const int so = sure ? v * kStep : (valid[v] ? v * kStep : 0);
+        const bool sure = kForm == kRagged || (!kCheckAll && v < kVpt - 1);
+        const int vo = sure ? TURNKL_OFF_V(v) : (valid[v] ? lane_off : 0);
+        const int so = sure ? TURNKL_OFF_S(v) : (valid[v] ? v * kStep : 0);
         xs[v].load(rs, vo, so);
         xt[v].load(rt, vo, so);
       }
@@ -471,6 +546,26 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     xs[v].fence();                                       \
     xt[v].fence();                                       \
   }
+#define TURNKL_BLOCK_SUMS(SS, AA, ST)                                         \
+  {                                                                           \
+    SS = wave_sum(SS);                                                        \
+    AA = wave_sum(AA);                                                        \
+    ST = wave_sum(ST);                                                        \
+    if (lane == 0) {                                                          \
+      s_sum[0][wid] = SS;                                                     \
+      s_sum[1][wid] = AA;                                                     \
+      s_sum[2][wid] = ST;                                                     \
+    }                                                                         \
+    __syncthreads();                                                          \
+    SS = s_sum[0][0];                                                         \
+    AA = s_sum[1][0];                                                         \
+    ST = s_sum[2][0];                                                         \
+    _Pragma("unroll") for (int w = 1; w < kRowWaves; ++w) {                   \
+      SS += s_sum[0][w];                                                      \
+      AA += s_sum[1][w];                                                      \
+      ST += s_sum[2][w];                                                      \
+    }                                                                         \
+  }
   // OFFSET (a literal): exponents against natural references RS, RT and the
   // exact difference against the double-float C2; otherwise RS, RT are
   // log2-unit references folded into the exponent FMA (C2 unused)
@@ -493,7 +588,12 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
           et = exp2_fast(fmaf(b, kLog2e, -(RT)));                             \
           d = a - b;                                                          \
         }                                                                     \
-        if (kCheckAll || v == kVpt - 1) {                                     \
+        if (TURNKL_EDGE(v)) {                                                 \
+          const unsigned own = own_mask(v == 0 ? bits_first : bits_last, j);  \
+          es = __uint_as_float(__float_as_uint(es) & own);                    \
+          et = __uint_as_float(__float_as_uint(et) & own);                    \
+          d = __uint_as_float(__float_as_uint(d) & own);                      \
+        } else if (kCheckAll || v == kVpt - 1) {                              \
           es = valid[v] ? es : 0.0f;                                          \
           et = valid[v] ? et : 0.0f;                                          \
           d = valid[v] ? d : 0.0f;                                            \
@@ -502,24 +602,11 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         AA = fmaf(es, d, AA);                                                 \
         ST += et;                                                             \
       }                                                                       \
+      /* keeps the compiler from taking one sum over all packs at a time,     \
+         with every unpacked value alive: over 200 more VGPRs */              \
+      if (kForm == kRagged) asm volatile("" : "+v"(SS), "+v"(AA), "+v"(ST));  \
     }                                                                         \
-    SS = wave_sum(SS);                                                        \
-    AA = wave_sum(AA);                                                        \
-    ST = wave_sum(ST);                                                        \
-    if (lane == 0) {                                                          \
-      s_sum[0][wid] = SS;                                                     \
-      s_sum[1][wid] = AA;                                                     \
-      s_sum[2][wid] = ST;                                                     \
-    }                                                                         \
-    __syncthreads();                                                          \
-    SS = s_sum[0][0];                                                         \
-    AA = s_sum[1][0];                                                         \
-    ST = s_sum[2][0];                                                         \
-    _Pragma("unroll") for (int w = 1; w < kRowWaves; ++w) {                   \
-      SS += s_sum[0][w];                                                      \
-      AA += s_sum[1][w];                                                      \
-      ST += s_sum[2][w];                                                      \
-    }                                                                         \
+    TURNKL_BLOCK_SUMS(SS, AA, ST)                                             \
   }
 
     float ms = -INFINITY, mt = -INFINITY;
@@ -546,16 +633,38 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       ms = -INFINITY;
       mt = -INFINITY;
       float bm = -INFINITY;
+      if constexpr (kForm == kRagged) {
+        // from memory, one pack at a time: unrolled over the registers, this
+        // path costs the ragged kernel over 100 VGPRs.  (A moved pack's
+        // foreign elements are the row's own too, so any may be the maximum.)
+#pragma unroll 1
+        for (int v = 0; v < kVpt && v * kRowThreads + tid < n_valid; ++v) {
+          P ya, yb;
+          const int off = (inside_row((int)col + (v * kRowThreads + tid) * kEpv, p.vocab - kEpv) - (int)col) * kEs;
+          ya.load(rs, off, 0);
+          yb.load(rt, off, 0);
 #pragma unroll
-      for (int v = 0; v < kVpt; ++v) {
+          for (int j = 0; j < kEpv; ++j) {
+            const float a = ya.get(j);
+            const float b = yb.get(j);
+            const bool take = (a > ms) | ((a == ms) & (b > bm));
+            ms = take ? a : ms;
+            bm = take ? b : bm;
+            mt = fmaxf(mt, b);
+          }
+        }
+      } else {
 #pragma unroll
-        for (int j = 0; j < kEpv; ++j) {
-          const float a = valid[v] ? xs[v].get(j) : -INFINITY;
-          const float b = valid[v] ? xt[v].get(j) : -INFINITY;
-          const bool take = (a > ms) | ((a == ms) & (b > bm));  // branch-free
-          ms = take ? a : ms;
-          bm = take ? b : bm;
-          mt = fmaxf(mt, b);
+        for (int v = 0; v < kVpt; ++v) {
+#pragma unroll
+          for (int j = 0; j < kEpv; ++j) {
+            const float a = valid[v] ? xs[v].get(j) : -INFINITY;
+            const float b = valid[v] ? xt[v].get(j) : -INFINITY;
+            const bool take = (a > ms) | ((a == ms) & (b > bm));  // branch-free
+            ms = take ? a : ms;
+            bm = take ? b : bm;
+            mt = fmaxf(mt, b);
+          }
         }
       }
 #pragma unroll
@@ -591,9 +700,39 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       c_b = bm;
       TURNKL_FENCE_ALL()
       __syncthreads();
-      TURNKL_CHUNK_SUMS(true, m2s, m2t, two_diff(c_a, c_b), ss, aa, st)
+      if constexpr (kForm == kRagged) {
+        const Float2 c2 = two_diff(c_a, c_b);
+        ss = 0.0f;
+        aa = 0.0f;
+        st = 0.0f;
+#pragma unroll 1
+        for (int v = 0; v < kVpt && v * kRowThreads + tid < n_valid; ++v) {
+          P ya, yb;
+          const int e = (int)col + (v * kRowThreads + tid) * kEpv;
+          const int at = inside_row(e, p.vocab - kEpv);
+          const unsigned bits = own_bits<kEpv>(e - at);
+          ya.load(rs, (at - (int)col) * kEs, 0);
+          yb.load(rt, (at - (int)col) * kEs, 0);
+#pragma unroll
+          for (int j = 0; j < kEpv; ++j) {
+            const float a = ya.get(j);
+            const float b = yb.get(j);
+            const bool own = (bits >> j) & 1u;
+            const float es = own ? exp2_fast((a - m2s) * kLog2e) : 0.0f;
+            const float et = own ? exp2_fast((b - m2t) * kLog2e) : 0.0f;
+            const float d = own ? diff_minus(a, b, c2) : 0.0f;
+            ss += es;
+            aa = fmaf(es, d, aa);
+            st += et;
+          }
+        }
+        TURNKL_BLOCK_SUMS(ss, aa, st)
+      } else {
+        TURNKL_CHUNK_SUMS(true, m2s, m2t, two_diff(c_a, c_b), ss, aa, st)
+      }
     }
 #undef TURNKL_CHUNK_SUMS
+#undef TURNKL_BLOCK_SUMS
 #undef TURNKL_FENCE_ALL
 #undef TURNKL_BLOCK_MAX2
 #pragma unroll
@@ -720,7 +859,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       __builtin_amdgcn_s_setprio(2);
       const float sc = p.wsc[row];
       const float l2 = log2f(r.ss) - log2f(fabsf(sc));
-      const float shift = row_offset ? l2 : fmaf(r_s, kLog2e, l2);
+      const float l2s = row_offset ? l2 : fmaf(r_s, kLog2e, l2);
       const unsigned flip = sc < 0.0f ? 0x80008000u : 0u;
       const auto rg = chunk_rsrc(static_cast<char*>(p.grad) + (row * p.ld_g + col) * kEs);
       if (!row_offset) {
@@ -732,10 +871,10 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
           for (int j = 0; j < kEpv; ++j) {
             const float a = xs[v].get(j);
             const float b = xt[v].get(j);
-            out[j] = exp2_fast(fmaf(a, kLog2e, -shift)) * ((a - b) - mu);
+            out[j] = exp2_fast(fmaf(a, kLog2e, -l2s)) * ((a - b) - mu);
           }
           const typename P::Data cur = P::encode(out, flip);
-          if (valid[v]) P::store(rg, lane_off, v * kStep, cur);
+          if (valid[v]) P::store(rg, TURNKL_OFF_V(v), TURNKL_OFF_S(v), cur);
           // keep the store here, so the next pack's work separates it from
           // any reuse of its data registers; the previous pack's data is free
           __builtin_amdgcn_sched_barrier(0);
@@ -759,16 +898,32 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         for (int v = 0; v < kVpt; ++v) {
           if (v * kRowThreads + tid >= n_valid) break;
           P ya, yb;
-          ya.load(rs2, lane_off, v * kStep);
-          yb.load(rt2, lane_off, v * kStep);
+          // a ragged row's pack that sticks out of the row: only its own
+          // elements are written, since a neighbour may have overwritten the
+          // shared ones (in place) before this pack was read
+          int shift = 0, off = lane_off + v * kStep;
+          if constexpr (kForm == kRagged) {
+            const int e = (int)col + (v * kRowThreads + tid) * kEpv;
+            const int at = inside_row(e, p.vocab - kEpv);
+            shift = e - at;
+            off = (at - (int)col) * kEs;
+          }
+          ya.load(rs2, off, 0);
+          yb.load(rt2, off, 0);
           float out[kEpv];
 #pragma unroll
           for (int j = 0; j < kEpv; ++j) {
             const float a = ya.get(j);
             const float b = yb.get(j);
-            out[j] = exp2_fast(fmaf(a - r_s, kLog2e, -shift)) * (diff_minus(a, b, c_row) - mu);
+            out[j] = exp2_fast(fmaf(a - r_s, kLog2e, -l2s)) * (diff_minus(a, b, c_row) - mu);
           }
-          P::store(rg, lane_off, v * kStep, P::encode(out, flip));
+          if (kForm != kRagged || shift == 0) {
+            P::store(rg, off, 0, P::encode(out, flip));
+          } else if constexpr (kForm == kRagged) {
+#pragma unroll
+            for (int j = 0; j < kEpv; ++j)
+              if (own_mask(own_bits<kEpv>(shift), j)) store_one<kBf16>(rg, off + j * kEs, out[j], flip);
+          }
           drain_stores();
         }
         carry = P::zero();
@@ -777,6 +932,9 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
   }
   drain_stores();
 }
+#undef TURNKL_EDGE
+#undef TURNKL_OFF_V
+#undef TURNKL_OFF_S
 
 // ---------------------------------------------------------------------------
 // launch
@@ -792,47 +950,66 @@ int cu_count() {
   return n;
 }
 
-template <bool kBf16, int kEpv, int kVpt, bool kCheckAll, bool kSplit = false>
-hipError_t launch_one(const RowParams& p, hipStream_t s) {
+// workgroups of a kernel that run on a CU at once
+template <auto kKernel>
+int occupancy() {
   static const int occ = [] {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, rowkl_kernel<kBf16, kEpv, kVpt, kCheckAll, kSplit>,
-                                                     kRowThreads, 0) != hipSuccess || n < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kKernel, kRowThreads, 0) != hipSuccess || n < 1)
       n = 1;
     return n;
   }();
+  return occ;
+}
+
+template <auto kKernel>
+hipError_t launch_tasks(const RowParams& p, hipStream_t s) {
   const long long tasks = (long long)p.n_rows * p.n_chunks;
-  long long grid = (long long)occ * cu_count();
+  long long grid = (long long)occupancy<kKernel>() * cu_count();
   if (grid > tasks) grid = tasks;
   if (grid < 1) return hipSuccess;
-  rowkl_kernel<kBf16, kEpv, kVpt, kCheckAll, kSplit><<<dim3((unsigned)grid), dim3(kRowThreads), 0, s>>>(p);
+  kKernel<<<dim3((unsigned)grid), dim3(kRowThreads), 0, s>>>(p);
   return hipGetLastError();
 }
 
+template <bool kBf16, int kEpv, int kVpt, RowForm kForm, bool kSplit = false>
+hipError_t launch_one(const RowParams& p, hipStream_t s) {
+  return launch_tasks<rowkl_kernel<kBf16, kEpv, kVpt, kForm, kSplit>>(p, s);
+}
+
+#ifndef TURNKL_RAGGED_ROWS
 // bf16: both load orders, each kernel checking which one the call uses;
 // fp32: the alternating order alone.
 template <bool kBf16, int kEpv, int kVpt>
-hipError_t launch_orders(const RowParams& p, hipStream_t s) {
+hipError_t launch_vector(const RowParams& p, hipStream_t s) {
   if constexpr (kBf16) {
     RowParams q = p;
     q.pick_order = 1;
-    if (hipError_t e = launch_one<kBf16, kEpv, kVpt, false, true>(q, s); e != hipSuccess) return e;
-    return launch_one<kBf16, kEpv, kVpt, false, false>(q, s);
+    if (hipError_t e = launch_one<kBf16, kEpv, kVpt, kAligned, true>(q, s); e != hipSuccess) return e;
+    return launch_one<kBf16, kEpv, kVpt, kAligned, false>(q, s);
   } else {
-    return launch_one<kBf16, kEpv, kVpt, false, false>(p, s);
+    return launch_one<kBf16, kEpv, kVpt, kAligned, false>(p, s);
   }
 }
+#else
+template <bool kBf16, int kEpv, int kVpt>
+hipError_t launch_vector(const RowParams& p, hipStream_t s) {
+  return launch_one<kBf16, kEpv, kVpt, kRagged>(p, s);
+}
+#endif
 
 template <bool kBf16, int kEpv>
 hipError_t launch_vpt(const RowParams& p, int vpt, hipStream_t s) {
   switch (vpt) {
 #define TURNKL_CASE(n) \
-    case n: return launch_orders<kBf16, kEpv, n>(p, s);
+    case n: return launch_vector<kBf16, kEpv, n>(p, s);
     TURNKL_CASE(1) TURNKL_CASE(2) TURNKL_CASE(3) TURNKL_CASE(4) TURNKL_CASE(5) TURNKL_CASE(6)
     TURNKL_CASE(7) TURNKL_CASE(8) TURNKL_CASE(9) TURNKL_CASE(10) TURNKL_CASE(11) TURNKL_CASE(12)
     TURNKL_CASE(13) TURNKL_CASE(14) TURNKL_CASE(15) TURNKL_CASE(16) TURNKL_CASE(17) TURNKL_CASE(18)
-    TURNKL_CASE(19) TURNKL_CASE(20) TURNKL_CASE(21) TURNKL_CASE(22) TURNKL_CASE(23) TURNKL_CASE(24)
-    TURNKL_CASE(25)
+    TURNKL_CASE(19) TURNKL_CASE(20) TURNKL_CASE(21) TURNKL_CASE(22)
+#ifndef TURNKL_RAGGED_ROWS
+    TURNKL_CASE(23) TURNKL_CASE(24) TURNKL_CASE(25)
+#endif
 #undef TURNKL_CASE
     default: return hipErrorInvalidValue;
   }
@@ -840,13 +1017,20 @@ hipError_t launch_vpt(const RowParams& p, int vpt, hipStream_t s) {
 
 }  // namespace
 
+#ifndef TURNKL_RAGGED_ROWS
 hipError_t launch_rows(const RowParams& p, const RowTiling& t, hipStream_t s) {
   if (p.n_rows == 0) return hipSuccess;
+  if (t.ragged) return launch_ragged_rows(p, t, s);
   if (!t.vector) {
-    return p.bf16 ? launch_one<true, 1, kScalarVpt, true>(p, s)
-                  : launch_one<false, 1, kScalarVpt, true>(p, s);
+    return p.bf16 ? launch_one<true, 1, kScalarVpt, kScalar>(p, s)
+                  : launch_one<false, 1, kScalarVpt, kScalar>(p, s);
   }
   return p.bf16 ? launch_vpt<true, 8>(p, t.vpt, s) : launch_vpt<false, 4>(p, t.vpt, s);
 }
+#else
+hipError_t launch_ragged_rows(const RowParams& p, const RowTiling& t, hipStream_t s) {
+  return p.bf16 ? launch_vpt<true, 8>(p, t.vpt, s) : launch_vpt<false, 4>(p, t.vpt, s);
+}
+#endif
 
 }  // namespace turnkl

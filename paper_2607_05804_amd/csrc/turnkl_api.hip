@@ -30,6 +30,9 @@ bool vpt_allowed(int v) { return v >= 1 && v <= kMaxVpt; }
 // per CU: 7.40 ms for 65,536 rows, same process).
 constexpr int kDefaultVmax = 25;
 
+// The same cap for ragged rows, whose kernel needs about 20 more VGPRs.
+constexpr int kRaggedVmax = 22;
+
 long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
 }  // namespace
 
@@ -82,6 +85,49 @@ RowTiling scalar_tiling(long long vocab) {
   t.min_chunk = vocab / t.n_chunks;
   t.align = 1;
   return t;
+}
+
+// Rows of any start and length.  With line_mask = 127 the packs lie on the
+// grid of 128-byte lines, so the number of packs of a row varies with its
+// start, by at most eight.  The kernel needs every chunk but a row's last at
+// least 256 (vpt - 1) packs long, and the last one longer than that for every
+// start (its last pack may stick out of the row and only a thread's first and
+// last packs are checked).  Where no boundaries satisfy this, the grid starts
+// at each row's first element (line_mask = 0): all rows then have the same
+// packs, and balanced chunks satisfy it by construction.
+RowTiling ragged_tiling(long long vocab, int dtype, uintptr_t start, long long stride) {
+  RowTiling t{};
+  t.ragged = true;
+  t.epv = dtype == TURNKL_BF16 ? 8 : 4;
+  const long long bytes = vocab * (16 / t.epv);
+  for (int mask : {127, 0}) {
+    const bool one_start = stride % 128 == 0 || mask == 0;
+    const long long pre = (long long)(start & (uintptr_t)mask);
+    const long long most = ceil_div((one_start ? pre : mask) + bytes, 16);
+    const long long least = ceil_div((one_start ? pre : 0) + bytes, 16);
+    const int k = (int)ceil_div(most, (long long)kRowThreads * kRaggedVmax);
+    for (int align : {64, 8, 1}) {
+      long long widest = 0, narrowest = most;
+      for (int c = 0; c < k; ++c) {
+        const long long lo = chunk_start(most, k, align, c);
+        const long long w = chunk_start(most, k, align, c + 1) - lo;
+        const long long w_min = c + 1 < k ? w : least - lo - 1;
+        widest = w > widest ? w : widest;
+        narrowest = w_min < narrowest ? w_min : narrowest;
+      }
+      const int vpt = (int)ceil_div(widest, kRowThreads);
+      if (vpt > kRaggedVmax || narrowest < (long long)kRowThreads * (vpt - 1)) continue;
+      t.n_chunks = k;
+      t.align = align;
+      t.vpt = vpt;
+      t.line_mask = mask;
+      t.packs = most;
+      t.chunk = widest * t.epv;
+      t.min_chunk = narrowest;
+      return t;
+    }
+  }
+  return t;  // not reached: the last grid with align = 1 always fits
 }
 
 namespace {
@@ -262,20 +308,37 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
                                    {turn_stats_out, (size_t)max_turns * sizeof(turnkl_turn_stat)}}))
     return TURNKL_ERR_ALIAS;
 
-  // ---- row tiling: 16-byte vectors when every row start is 16-byte aligned
+  // ---- row tiling: 16-byte vectors; whole packs when every row start is
+  // 16-byte aligned and the vocabulary a multiple of a pack
   RowTiling tiling = vector_tiling(vocab, dtype, t_vpt_override);
+  int slot_chunks = 0;  // chunks per row that the workspace and the limits count
   {
     const long long epv = tiling.epv;
     bool ok = vector_possible(tiling, vocab) && ld_student % epv == 0 && ld_teacher % epv == 0;
     ok = ok && ((uintptr_t)student_logits & 15u) == 0 && ((uintptr_t)teacher_logits & 15u) == 0;
     if (grad_out) ok = ok && ld_grad % epv == 0 && ((uintptr_t)grad_out & 15u) == 0;
-    if (!ok) tiling = scalar_tiling(vocab);
+    // Other rows take the 16-byte loads of the ragged path, down to one pack
+    // per row: at V = 50,257 the whole call takes 280 us for 6,000 bf16 rows
+    // packed without padding (element-wise path: 724 us) and 265 us for 3,000
+    // fp32 rows at a stride of 50,304 (374 us).
+    if (!ok) {
+      tiling = scalar_tiling(vocab);
+      if (vocab >= epv && tiling.n_chunks <= kMaxChunks) {
+        // the limits below and the workspace stay those of the element-wise
+        // path, which has at least as many chunks
+        slot_chunks = tiling.n_chunks;
+        const void* lines = grad_out ? grad_out : student_logits;
+        tiling = ragged_tiling(vocab, dtype, (uintptr_t)lines,
+                               (long long)(grad_out ? ld_grad : ld_student) * (long long)es);
+      }
+    }
   }
-  if (tiling.n_chunks > kMaxChunks) return TURNKL_ERR_INVALID_ARG;
+  if (slot_chunks == 0) slot_chunks = tiling.n_chunks;
+  if (slot_chunks > kMaxChunks) return TURNKL_ERR_INVALID_ARG;
   if (n_tokens > 0 && (ld_student > 0x7FFFFFFFll || ld_teacher > 0x7FFFFFFFll ||
                        (grad_out && ld_grad > 0x7FFFFFFFll)))
     return TURNKL_ERR_INVALID_ARG;
-  if ((unsigned long long)n_tokens * (unsigned long long)tiling.n_chunks > 0x7FFFFFFFull)
+  if ((unsigned long long)n_tokens * (unsigned long long)slot_chunks > 0x7FFFFFFFull)
     return TURNKL_ERR_INVALID_ARG;
 
   SegParams sp{traj_id, turn_id, loss_mask, nullptr, (long long)n_tokens, max_turns, 0, 0, 0.0};
@@ -288,7 +351,7 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
     return rc;
 
   // the layout of this call: exchange slots for the path it takes
-  const Layout L = make_layout(n_tokens, tiling.n_chunks > 1 ? tiling.n_chunks : 0, 0, max_turns);
+  const Layout L = make_layout(n_tokens, slot_chunks > 1 ? slot_chunks : 0, 0, max_turns);
   if (noalloc) {
     if (L.total > kScratchBytes) return TURNKL_ERR_SCRATCH;
     workspace = scratch_address();
@@ -318,9 +381,11 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
   rp.hdr = ws.hdr;
   rp.slots = ws.slots;
   rp.n_rows = (int)n_tokens;
-  rp.n_packs = (int)(vocab / tiling.epv);
+  rp.n_packs = (int)(tiling.ragged ? tiling.packs : vocab / tiling.epv);
   rp.n_chunks = tiling.n_chunks;
   rp.align = tiling.align;
+  rp.vocab = (int)vocab;
+  rp.line_mask = tiling.line_mask;
   rp.bf16 = dtype == TURNKL_BF16;
   rp.lse = ex.lse;
   rp.spin_limit = t_spin_limit > 0 ? t_spin_limit : kDefaultSpinLimit;

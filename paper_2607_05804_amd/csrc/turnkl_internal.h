@@ -190,6 +190,9 @@ struct RowTiling {
   long long min_chunk;  // packs of the narrowest chunk
   int n_chunks;
   int align;    // chunk boundaries are multiples of this many packs (see chunk_start)
+  bool ragged;      // 16-byte vectors on rows of any start and length (>= one vector)
+  int line_mask;    // ragged: the packs' grid starts at a row's address & ~line_mask
+  long long packs;  // ragged: packs of a row at most
 };
 
 // First pack of chunk c (0 <= c <= n_chunks) of a row of n_packs packs: the
@@ -209,6 +212,9 @@ __host__ __device__ inline long long chunk_start(long long n_packs, int n_chunks
 // Tiling of the vector path for a given vectors-per-thread (0 = automatic).
 RowTiling vector_tiling(long long vocab, int dtype, int vpt);
 RowTiling scalar_tiling(long long vocab);
+// Tiling of the ragged path; `start` and `stride` are the address and the row
+// stride in bytes of the matrix whose lines the packs follow.
+RowTiling ragged_tiling(long long vocab, int dtype, uintptr_t start, long long stride);
 
 // ---------------------------------------------------------------------------
 // launches (each returns hipSuccess or the launch error)
@@ -277,6 +283,8 @@ struct RowParams {
   int n_packs;   // vocab / elements per pack
   int n_chunks;  // <= kMaxChunks
   int align;     // chunk boundary alignment in packs (chunk_start)
+  int vocab;     // ragged rows only, with line_mask: see RowTiling
+  int line_mask;
   int bf16;
   int spin_limit;  // polls of a missing row-mate partial before the call times out
   int pick_order;  // 1: one of two launches (one per load order) that picks by
@@ -289,6 +297,7 @@ struct RowParams {
 constexpr int kDefaultSpinLimit = 1 << 22;
 
 hipError_t launch_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
+hipError_t launch_ragged_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 
 // Top-K path (the teacher's top-K support; both distributions renormalised on
 // it).  The row kernel writes each supervised row's scaled gradient on the
