@@ -12,8 +12,8 @@
 //             of both distributions with wave shuffles, writes KL_i and
 //             grad_scale * w_i * dKL_i/da on the support to the stage (the
 //             caller's sparse output, or the workspace);
-// topk_fill   zero-fills the vocab columns of every dense gradient row with
-//             16-byte streaming stores;
+// topk_fill   (three forms) zero-fills the vocab columns of every dense
+//             gradient row with 16-byte stores;
 // topk_scatter  writes the staged support values of each supervised row.
 //
 // Order.  An out-of-place dense gradient is zero-filled first, and topk_rows
@@ -22,6 +22,8 @@
 // stages the values, then the fill and the scatter overwrite the rows.
 
 #include <hip/hip_bf16.h>
+
+#include <type_traits>
 
 #include "block_ops.h"
 #include "turnkl_internal.h"
@@ -159,46 +161,73 @@ __global__ __launch_bounds__(kThreads) void topk_rows(TopkParams p) {
   }
 }
 
-// Zero-fill of the dense gradient rows (grid-stride over rows): a plain
-// streaming store of vocab columns per row.  kVec: the row starts are 16-byte
-// aligned and V is a whole number of 16-byte packs, so the fill uses 16-byte
-// stores.
-template <bool kBf16, bool kVec>
-__global__ __launch_bounds__(kThreads) void topk_fill(TopkParams p) {
-  if (p.hdr->err_key != kNoError) return;
-  constexpr int kEs = kBf16 ? 2 : 4;
-  constexpr int kEpv = 16 / kEs;
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  for (long long row = blockIdx.x; row < p.n_rows; row += gridDim.x) {
-    char* g = static_cast<char*>(p.grad) + row * p.ld_g * kEs;
-    if (kVec) {
-      const long long packs = p.vocab / kEpv;
-      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g, 0, 0x7FFFFFFF, 0x00020000);
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      for (long long v = threadIdx.x; v < packs; v += kThreads)
-        __builtin_amdgcn_raw_buffer_store_b128(z, rsrc, (int)(v * 16), 0, 2 /* nt */);
-    } else {
-      for (long long v = threadIdx.x; v < p.vocab; v += kThreads) {
-        if (kBf16) reinterpret_cast<unsigned short*>(g)[v] = 0;
-        else reinterpret_cast<float*>(g)[v] = 0.0f;
-      }
-    }
+// Zero-fill of the dense gradient, bound by HBM writes.  One 16-byte store per
+// thread, 4 KiB per workgroup, workgroups in address order: the stores in
+// flight then cover one moving window of a few MiB, which the memory writes at
+// 6.75 TB/s (19.9 GB).  Fewer, longer-lived workgroups spread the window over
+// the whole matrix and lose DRAM page locality: a grid-stride loop over 32,768
+// workgroups reaches 5.7 TB/s, two stores per thread 6.0, four 5.9.  The
+// stores are nontemporal: default stores fill slightly faster (6.85 TB/s) but
+// leave dirty lines that the support values' stores then wait for (4,166 rows
+// of 32,000 in bf16: 110 us a call, nontemporal 90, 94 before; 16,384 rows of
+// 151,936: 838, 801 and 892; 6,000 of 50,257: 171, 144 and 209).
+//
+// Out of place the fill does not look at the error key: a load before the
+// store would hold each short workgroup, and the gradient of a call with a
+// data error is unspecified.  In place it must not overwrite the logits then.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr long long kFillBlocks = 1 << 23;  // a launch holds fewer than 2^32 threads
+
+// Rows without padding between them: `n_packs` 16-byte packs from p.grad
+// rounded up to one, and the elements before and after them.
+template <bool kBf16>
+__global__ __launch_bounds__(kThreads) void topk_fill_flat(TopkParams p, long long head, long long n_packs,
+                                                           long long n_elems) {
+  using E = typename std::conditional<kBf16, unsigned short, float>::type;
+  constexpr int kEpv = 16 / (int)sizeof(E);
+  if (!p.direct && p.hdr->err_key != kNoError) return;
+  E* const g = static_cast<E*>(p.grad);
+  const long long i0 = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (i0 < kEpv) {
+    if (i0 < head) g[i0] = E(0);
+    const long long tail = head + n_packs * kEpv + i0;
+    if (tail < n_elems) g[tail] = E(0);
   }
-  drain_stores();
+  const u32x4 z = {0u, 0u, 0u, 0u};
+  for (long long i = i0; i < n_packs; i += (long long)gridDim.x * kThreads)  // one turn up to kFillBlocks
+    __builtin_nontemporal_store(z, reinterpret_cast<u32x4*>(g + head) + i);
 }
 
-// Zero-fill of a dense gradient whose rows are contiguous (ld == vocab): one
-// flat region of n_rows * vocab elements, 16-byte streaming stores over a
-// grid-stride loop (the fastest write pattern measured on the device).
-__global__ __launch_bounds__(kThreads) void topk_fill_flat(TopkParams p, long long n_packs) {
-  if (p.hdr->err_key != kNoError) return;
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  u32x4* g = static_cast<u32x4*>(p.grad);
+// Rows at any stride and start, at least one pack long: one workgroup per
+// 256 packs of a row, on the grid of 128-byte lines; a pack that sticks out of
+// the row is moved inside it (its neighbour's elements are zeroed twice).
+template <bool kBf16>
+__global__ __launch_bounds__(kThreads) void topk_fill_rows(TopkParams p, unsigned per_row, long long blocks) {
+  constexpr int kEs = kBf16 ? 2 : 4;
+  constexpr int kEpv = 16 / kEs;
+  if (!p.direct && p.hdr->err_key != kNoError) return;
   const u32x4 z = {0u, 0u, 0u, 0u};
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n_packs;
-       i += (long long)gridDim.x * kThreads)
-    __builtin_nontemporal_store(z, g + i);
-  drain_stores();
+  for (long long b = blockIdx.x; b < blocks; b += gridDim.x) {  // one turn up to kFillBlocks
+    const long long row = b / per_row;
+    char* const g = static_cast<char*>(p.grad) + row * p.ld_g * kEs;
+    const int pre = (int)(reinterpret_cast<uintptr_t>(g) & 127u) / kEs;
+    int e = (int)((unsigned)(b - row * per_row) * kThreads + threadIdx.x) * kEpv - pre;
+    if (e <= -kEpv || e >= p.vocab) continue;
+    e = e < 0 ? 0 : (e > p.vocab - kEpv ? p.vocab - kEpv : e);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g, 0, 0x7FFFFFFF, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(z, rsrc, e * kEs, 0, 2 /* nt */);
+  }
+}
+
+// Rows shorter than a pack, with padding between them.
+template <bool kBf16>
+__global__ __launch_bounds__(kThreads) void topk_fill_short(TopkParams p) {
+  using E = typename std::conditional<kBf16, unsigned short, float>::type;
+  if (p.hdr->err_key != kNoError) return;
+  const long long row = (long long)blockIdx.x * kThreads + threadIdx.x;  // at most 2^31 rows
+  if (row >= p.n_rows) return;
+  E* const g = static_cast<E*>(p.grad) + row * p.ld_g;
+  for (int v = 0; v < p.vocab; ++v) g[v] = E(0);
 }
 
 // Scatter of the staged support values into the zero-filled rows of
@@ -242,14 +271,29 @@ int grid_for(long long items, int per_block, int cap) {
   return (int)(g < cap ? g : cap);
 }
 
-void launch_fill_rows(const TopkParams& p, bool vec, hipStream_t s) {
-  const int fill_grid = grid_for(p.n_rows, 1, 32768);
-  if (p.bf16) {
-    if (vec) topk_fill<true, true><<<fill_grid, kThreads, 0, s>>>(p);
-    else topk_fill<true, false><<<fill_grid, kThreads, 0, s>>>(p);
+dim3 fill_grid(long long blocks) {
+  return dim3((unsigned)(blocks < kFillBlocks ? blocks : kFillBlocks));
+}
+
+template <bool kBf16>
+void launch_fill(const TopkParams& p, hipStream_t s) {
+  constexpr int kEs = kBf16 ? 2 : 4;
+  constexpr int kEpv = 16 / kEs;
+  const long long elems = (long long)p.n_rows * p.vocab;
+  // elements before the first 16-byte boundary (none when no element starts on one)
+  const long long head = (long long)((16 - ((uintptr_t)p.grad & 15u)) & 15u) / kEs;
+  if ((p.ld_g == p.vocab || p.n_rows == 1) && (uintptr_t)p.grad % kEs == 0 && elems >= 2 * kEpv) {
+    const long long packs = (elems - head) / kEpv;
+    topk_fill_flat<kBf16><<<fill_grid((packs + kThreads - 1) / kThreads), kThreads, 0, s>>>(
+        p, head, packs, elems);
+  } else if (p.vocab >= kEpv) {
+    // the packs of a row that starts at the end of a line
+    const long long packs = (127 / kEs + (long long)p.vocab + kEpv - 1) / kEpv;
+    const unsigned per_row = (unsigned)((packs + kThreads - 1) / kThreads);
+    const long long blocks = (long long)p.n_rows * per_row;
+    topk_fill_rows<kBf16><<<fill_grid(blocks), kThreads, 0, s>>>(p, per_row, blocks);
   } else {
-    if (vec) topk_fill<false, true><<<fill_grid, kThreads, 0, s>>>(p);
-    else topk_fill<false, false><<<fill_grid, kThreads, 0, s>>>(p);
+    topk_fill_short<kBf16><<<dim3((unsigned)((p.n_rows + kThreads - 1) / kThreads)), kThreads, 0, s>>>(p);
   }
 }
 
@@ -277,14 +321,8 @@ hipError_t launch_topk_rows(const TopkParams& p, hipStream_t s) {
 
 hipError_t launch_topk_fill(const TopkParams& p, hipStream_t s) {
   if (p.n_rows == 0 || !p.grad) return hipSuccess;
-  const int es = p.bf16 ? 2 : 4;
-  const bool vec = ((uintptr_t)p.grad % 16 == 0) && (p.ld_g * es) % 16 == 0 && (p.vocab * es) % 16 == 0;
-  if (vec && p.ld_g == p.vocab) {
-    const long long packs = (long long)p.n_rows * p.vocab * es / 16;
-    topk_fill_flat<<<grid_for(packs, kThreads, 32768), kThreads, 0, s>>>(p, packs);
-  } else {
-    launch_fill_rows(p, vec, s);
-  }
+  if (p.bf16) launch_fill<true>(p, s);
+  else launch_fill<false>(p, s);
   return hipGetLastError();
 }
 
