@@ -7,7 +7,8 @@
 // turn-normalised blend of Sec. 5.2 / App. D Algorithm 1 expanded per token:
 //   w_i = m_i / B * ((1 - alpha) / N_b + alpha / (T_b * n_bt)).
 //
-// Kernels, in launch order (all integer work is exact, so the table is unique):
+// Kernels, in launch order (all integer work is exact, so the table is unique;
+// small batches run seg_one instead of all of them):
 //   seg_count   per 1024-token tile: segment starts and the earliest id/mask
 //               error of the tile; clears the per-segment counters; the first
 //               workgroup resets the workspace header.
@@ -229,10 +230,25 @@ __global__ __launch_bounds__(kSegThreads) void seg_write(SegParams p, Ws ws, lon
     if (const int n = s_nsup[k]) atomicAdd(&ws.seg_nsup[first + k], n);
 }
 
+// For each head among the wave's segments with n > 0: add(head, how many
+// segments, their sum of n), in one lane.
+template <typename Add>
+__device__ inline void wave_by_head(int head, int n, Add add) {
+  const int lane = threadIdx.x & (kWave - 1);
+  unsigned long long todo = __ballot(n > 0);
+  while (todo) {
+    const int leader = __builtin_ctzll(todo);
+    const int h = __shfl(head, leader, kWave);
+    const unsigned long long same = __ballot(n > 0 && head == h);
+    const int sum_n = wave_sum((same >> lane) & 1ull ? n : 0);
+    if (lane == leader) add(h, __popcll(same), sum_n);
+    todo &= ~same;
+  }
+}
+
 __global__ __launch_bounds__(kSegThreads) void seg_link(SegParams p, Ws ws) {
   __shared__ int s_red[kSegThreads / kWave];
   const int n_seg = ws.hdr->n_seg;
-  const int lane = threadIdx.x & (kWave - 1);
   int sup_total = 0;
   // every lane of a wave runs the same iterations (the per-trajectory sums
   // below are wave-wide)
@@ -268,18 +284,10 @@ __global__ __launch_bounds__(kSegThreads) void seg_link(SegParams p, Ws ws) {
     // T_b and N_b: the wave's supervised segments summed per trajectory head,
     // one atomic pair per head; the add that lifts N_b from zero counts the
     // trajectory in B
-    unsigned long long todo = __ballot(n > 0);
-    while (todo) {
-      const int leader = __builtin_ctzll(todo);
-      const int h = __shfl(head, leader, kWave);
-      const unsigned long long same = __ballot(n > 0 && head == h);
-      const int sum_n = wave_sum((same >> lane) & 1ull ? n : 0);
-      if (lane == leader) {
-        atomicAdd(&ws.traj_T[h], __popcll(same));
-        if (atomicAdd(&ws.traj_N[h], sum_n) == 0) atomicAdd(&ws.hdr->b_eff, 1);
-      }
-      todo &= ~same;
-    }
+    wave_by_head(head, n, [&](int h, int n_turns, int sum_n) {
+      atomicAdd(&ws.traj_T[h], n_turns);
+      if (atomicAdd(&ws.traj_N[h], sum_n) == 0) atomicAdd(&ws.hdr->b_eff, 1);
+    });
   }
   sup_total = block_sum<kSegThreads>(sup_total, s_red);
   if (threadIdx.x == 0 && sup_total) atomicAdd(&ws.hdr->n_sup, sup_total);
@@ -325,6 +333,298 @@ __global__ __launch_bounds__(kSegThreads) void token_weights(SegParams p, Ws ws,
   }
 }
 
+// ---------------------------------------------------------------------------
+// Batches of at most kOneTokens tokens: all of the above in one kernel.  One
+// workgroup holds the whole table (in LDS up to kOneSegs segments, beyond in
+// the workspace), the others clear the exchange slots and the per-token KL.
+// The four or five kernels above take 5 to 8 us each, nearly all of it launch
+// and memory latency; this one replaces them up to 8,192 tokens: 160 tokens of
+// 1,024 fp32 logits, whole call 35.9 -> 24.9 us; 4,096 tokens of the top-K call
+// 47 -> 33; 8,192 tokens 50 -> 40 (and 154 -> 142 with 1,024 bf16 logits).  At
+// 16,384 tokens one workgroup no longer beats the tiled kernels (56.5 against
+// 55.9 us).  A table beyond LDS costs its latency again: 8,192 tokens in 4,160
+// segments take 168 us either way.
+
+constexpr int kOneThreads = 1024;
+constexpr int kOneMax = 8;  // tokens per thread
+constexpr int kOneSegs = 4096;   // 144 KiB of LDS
+constexpr int kOneTurns = 2048;  // turn indices under a support floor
+
+// One entry per segment; the trajectory sums are at its first segment.  In LDS
+// the weights take the place of start and traj, which are copied out by then.
+struct SegTable {
+  int *start, *end, *traj, *turn, *nsup, *head, *T, *N, *Tv;
+  float *w, *wsc;
+};
+
+// A thread's tokens r * kOneThreads + threadIdx.x, r < rounds: their ids, and bit
+// r says whether the token starts a segment, is the last of one, is supervised,
+// is padding (or beyond the batch).
+template <int kMax>
+struct OwnTokens {
+  int traj[kMax], turn[kMax];
+  unsigned start, last, sup, pad;
+};
+
+// an add that only this workgroup needs to see before the kernel ends
+__device__ inline void add_here(int* x, int n) {
+  __hip_atomic_fetch_add(x, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ inline bool bit(unsigned m, int j) { return (m >> j) & 1u; }
+
+// Everything after the segment count.  before[r * waves + w]: segments that
+// start before the tokens of wave w in round r.  kLds: the table is in LDS,
+// otherwise in the workspace.
+template <bool kLds, int kMax>
+__device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, const SegTable& t, int* s_surv,
+                                          const int* before, int n_seg, const OwnTokens<kMax>& own, int rounds,
+                                          unsigned long long err, double alpha, float grad_scale) {
+  constexpr int kWaves = kOneThreads / kWave;
+  __shared__ unsigned long long s_err[kWaves];
+  __shared__ int s_b[kWaves], s_n[kWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  for (int s = tid; s < n_seg; s += kOneThreads) {
+    t.nsup[s] = 0;
+    t.T[s] = 0;
+    t.N[s] = 0;
+    t.Tv[s] = 0;
+  }
+  if (p.floor_on)
+    for (int k = tid; k < p.max_turns; k += kOneThreads) s_surv[k] = 0;
+  __syncthreads();
+  int seg[kMax];
+#pragma unroll
+  for (int r = 0; r < kMax; ++r) {
+    if (r >= rounds) continue;
+    const int i = r * kOneThreads + tid;
+    const bool start = bit(own.start, r), pad = bit(own.pad, r);
+    const unsigned long long starts = __ballot(start);
+    const unsigned long long cuts = __ballot(start || pad);
+    const unsigned long long sup = __ballot(bit(own.sup, r));
+    const unsigned long long upto = ~0ull >> (kWave - 1 - lane);  // lanes 0 .. lane
+    seg[r] = before[r * kWaves + tid / kWave] + __popcll(starts & upto) - 1;
+    if (start) {
+      t.start[seg[r]] = i;
+      t.traj[seg[r]] = own.traj[r];
+      t.turn[seg[r]] = own.turn[r];
+    }
+    if (bit(own.last, r)) t.end[seg[r]] = i + 1;
+    // the first lane of each run of one segment adds the run's supervised tokens
+    const unsigned long long after = cuts & ~upto;
+    const unsigned long long run = (after ? (after & -after) - 1ull : ~0ull) & ~(upto >> 1);
+    const int n = __popcll(sup & run);
+    if (!pad && (start || lane == 0) && n) add_here(&t.nsup[seg[r]], n);
+  }
+  __syncthreads();
+  int n_sup = 0;
+  // every lane of a wave runs the same iterations (the sums by head are wave-wide)
+  for (int s0 = 0; s0 < n_seg; s0 += kOneThreads) {
+    const int s = s0 + tid;
+    int n = 0, lo = 0;
+    if (s < n_seg) {
+      const int b = t.traj[s];
+      const int turn = t.turn[s];
+      if (s > 0) {
+        const int pb = t.traj[s - 1];
+        const int pt = t.turn[s - 1];
+        if (b < pb || (b == pb && turn <= pt)) {
+          const unsigned long long e = err_key(t.start[s], kPrioUnsorted);
+          err = e < err ? e : err;
+        }
+      }
+      int hi = s;  // first segment of this trajectory, as in seg_link
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (t.traj[mid] < b) lo = mid + 1; else hi = mid;
+      }
+      t.head[s] = lo;
+      if (p.success && lo != s && (p.success[t.start[s]] != 0) != (p.success[t.start[lo]] != 0)) {
+        const unsigned long long e = err_key(t.start[s], kPrioOutcome);
+        err = e < err ? e : err;
+      }
+      n = t.nsup[s];
+      n_sup += n;
+      if (n > 0 && p.floor_on && turn >= 0 && turn < p.max_turns) add_here(&s_surv[turn], 1);
+    }
+    if (kLds) {
+      if (n > 0) {
+        add_here(&t.T[lo], 1);
+        add_here(&t.N[lo], n);
+      }
+    } else {  // global atomics on one address take about 10 ns each
+      wave_by_head(lo, n, [&](int h, int n_turns, int sum_n) {
+        add_here(&t.T[h], n_turns);
+        add_here(&t.N[h], sum_n);
+      });
+    }
+  }
+  __syncthreads();
+  int b_eff = 0;
+  for (int s = tid; s < n_seg; s += kOneThreads) b_eff += t.N[s] > 0 ? 1 : 0;
+  b_eff = wave_sum(b_eff);
+  n_sup = wave_sum(n_sup);
+  err = wave_min_u64(err);
+  if ((tid & (kWave - 1)) == 0) {
+    s_b[tid / kWave] = b_eff;
+    s_n[tid / kWave] = n_sup;
+    s_err[tid / kWave] = err;
+  }
+  __syncthreads();
+  b_eff = 0;
+  n_sup = 0;
+  err = kNoError;
+  for (int w = 0; w < kWaves; ++w) {
+    b_eff += s_b[w];
+    n_sup += s_n[w];
+    err = s_err[w] < err ? s_err[w] : err;
+  }
+  if (tid == 0) {
+    volatile Header* h = ws.hdr;
+    h->err_key = err;
+    h->ticket = 0u;
+    h->n_seg = n_seg;
+    h->b_eff = b_eff;
+    h->n_sup = n_sup;
+  }
+  const int n_min = p.floor_on ? support_n_min(p, b_eff) : 0;
+  if (p.floor_on) {
+    for (int k = tid; k < p.max_turns; k += kOneThreads) ws.turn_surv[k] = s_surv[k];
+    for (int s0 = 0; s0 < n_seg && err == kNoError; s0 += kOneThreads) {
+      const int s = s0 + tid;
+      const bool valid = s < n_seg && t.nsup[s] > 0 && s_surv[t.turn[s]] >= n_min;
+      const int head = valid ? t.head[s] : 0;
+      if (kLds) {
+        if (valid) add_here(&t.Tv[head], 1);
+      } else {
+        wave_by_head(head, valid ? 1 : 0, [&](int h, int n_turns, int) { add_here(&t.Tv[h], n_turns); });
+      }
+    }
+    __syncthreads();
+  }
+  const double inv_b = b_eff > 0 ? 1.0 / (double)b_eff : 0.0;
+  for (int s = tid; s < n_seg; s += kOneThreads) {
+    const int h = t.head[s];
+    const int n = t.nsup[s];
+    const int start = t.start[s];
+    if (kLds) {
+      ws.seg_start[s] = start;
+      ws.seg_traj[s] = t.traj[s];
+      ws.seg_turn[s] = t.turn[s];
+      ws.seg_nsup[s] = n;
+      ws.seg_head[s] = h;
+      ws.traj_T[s] = t.T[s];
+      ws.traj_N[s] = t.N[s];
+      ws.traj_Tv[s] = t.Tv[s];
+    }
+    ws.seg_len[s] = t.end[s] - start;
+    float w = 0.0f, wsc = 0.0f;
+    if (n > 0 && err == kNoError) {
+      const double n_b = (double)t.N[h];
+      TurnTerm u{(double)t.T[h], true};
+      if (p.floor_on) u = TurnTerm{(double)t.Tv[h], s_surv[t.turn[s]] >= n_min};
+      const double x = inv_b * ((1.0 - alpha) / n_b + turn_part(alpha, u, (double)n, n_b));
+      w = (float)x;
+      wsc = (float)(x * (double)grad_scale);
+    }
+    t.w[s] = w;
+    t.wsc[s] = wsc;
+  }
+  if (err != kNoError) return;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kMax; ++r) {
+    const int i = r * kOneThreads + tid;
+    if (i >= (int)p.n) continue;
+    const bool m = bit(own.sup, r);
+    ws.w[i] = m ? t.w[seg[r]] : 0.0f;
+    ws.wsc[i] = m ? t.wsc[seg[r]] : 0.0f;
+  }
+}
+
+template <int kMax>
+__global__ __launch_bounds__(kOneThreads) void seg_one(SegParams p, Ws ws, double alpha, float grad_scale,
+                                                       int slot_words, float* kl, int rounds) {
+  const int tid = threadIdx.x;
+  const int n = (int)p.n;
+  if (blockIdx.x > 0) {
+    const long long at = (long long)(blockIdx.x - 1) * kOneThreads + tid;
+    const long long step = (long long)(gridDim.x - 1) * kOneThreads;
+    for (long long q = at; q < (long long)n * slot_words; q += step) ws.slots[q] = 0ull;
+    for (long long q = at; q < n; q += step) kl[q] = 0.0f;
+    return;
+  }
+  __shared__ int s_table[9][kOneSegs];
+  __shared__ int s_surv[kOneTurns];
+  __shared__ int s_scan[kOneThreads / kWave];
+  constexpr int kWaves = kOneThreads / kWave;
+  __shared__ int s_before[kMax * kWaves];
+  // the tokens and both neighbours, every load before the first use
+  OwnTokens<kMax> own;
+  own.start = own.last = own.sup = own.pad = 0u;
+  const int lane = tid & (kWave - 1);
+  int eb[kMax], et[kMax];  // lane 0: of the token before, lane 63: of the token after
+  unsigned char m[kMax];
+#pragma unroll
+  for (int r = 0; r < kMax; ++r) {
+    const int i = r * kOneThreads + tid;
+    const int e = lane == 0 ? i - 1 : i + 1;
+    const bool in = r < rounds && i < n;
+    const bool edge = r < rounds && (lane == 0 || lane == kWave - 1) && e >= 0 && e < n;
+    own.traj[r] = in ? p.traj[i] : -1;
+    own.turn[r] = in ? p.turn[i] : 0;
+    m[r] = in ? p.mask[i] : 0;
+    eb[r] = edge ? p.traj[e] : -1;
+    et[r] = edge ? p.turn[e] : 0;
+  }
+  unsigned long long err = kNoError;
+#pragma unroll
+  for (int r = 0; r < kMax; ++r) {
+    const int i = r * kOneThreads + tid;
+    const int b = own.traj[r], t = own.turn[r];
+    const int ub = __shfl_up(b, 1, kWave), ut = __shfl_up(t, 1, kWave);
+    const int db = __shfl_down(b, 1, kWave), dt = __shfl_down(t, 1, kWave);
+    const int pb = lane == 0 ? eb[r] : ub, pt = lane == 0 ? et[r] : ut;
+    const int nb = lane == kWave - 1 ? eb[r] : db, nt = lane == kWave - 1 ? et[r] : dt;
+    unsigned long long e = kNoError;
+    bool start = false;
+    if (b < 0) {
+      if (m[r]) e = err_key(i, kPrioPadMask);
+      own.pad |= 1u << r;
+    } else {
+      if (t < 0 || t >= p.max_turns) e = err_key(i, kPrioTurnRange);
+      start = i == 0 || pb != b || pt != t;
+      const bool last = i + 1 == n || nb != b || nt != t;
+      if (p.success && !start && e == kNoError && ((p.success[i] != 0) != (p.success[i - 1] != 0)))
+        e = err_key(i, kPrioOutcome);
+      own.start |= (start ? 1u : 0u) << r;
+      own.last |= (last ? 1u : 0u) << r;
+      own.sup |= (m[r] ? 1u : 0u) << r;
+    }
+    err = e < err ? e : err;
+    const unsigned long long starts = __ballot(start);
+    if (lane == 0) s_before[r * kWaves + tid / kWave] = __popcll(starts);
+  }
+  __syncthreads();
+  int n_seg;
+  const int k = tid < rounds * kWaves ? s_before[tid] : 0;
+  const int before = block_exclusive_scan<kOneThreads>(k, s_scan, &n_seg);
+  if (tid < rounds * kWaves) s_before[tid] = before;
+  if (n_seg <= kOneSegs) {
+    const SegTable tab{s_table[0], s_table[1], s_table[2], s_table[3], s_table[4], s_table[5],
+                       s_table[6], s_table[7], s_table[8], reinterpret_cast<float*>(s_table[0]),
+                       reinterpret_cast<float*>(s_table[2])};
+    one_table<true, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
+  } else {
+    // the weights' place: the segment moments, which are written later
+    float* const w = reinterpret_cast<float*>(ws.seg_stat);
+    const SegTable tab{ws.seg_start, ws.tok_seg, ws.seg_traj, ws.seg_turn, ws.seg_nsup, ws.seg_head,
+                       ws.traj_T, ws.traj_N, ws.traj_Tv, w, w + n};
+    one_table<false, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
+  }
+}
+
 int grid_for(long long items, int per_block, int cap) {
   long long g = (items + per_block - 1) / per_block;
   if (g < 1) g = 1;
@@ -350,6 +650,21 @@ hipError_t launch_segments(const SegParams& p, const Ws& ws, long long nblk, hip
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (!p.floor_on) return hipSuccess;
   seg_valid<<<grid_for(p.n, kSegThreads, 1024), kSegThreads, 0, s>>>(p, ws);
+  return hipGetLastError();
+}
+
+bool one_workgroup(const SegParams& p) {
+  return p.n <= kOneThreads * kOneMax && (!p.floor_on || p.max_turns <= kOneTurns);
+}
+
+hipError_t launch_one_workgroup(const SegParams& p, const Ws& ws, double alpha, float grad_scale,
+                                int n_chunks, float* kl, hipStream_t s) {
+  const int slot_words = n_chunks > 1 ? n_chunks * kExchangeWords : 0;
+  const int per = (int)((p.n + kOneThreads - 1) / kOneThreads);
+  // a workgroup clears about 32 KiB
+  const int grid = 1 + grid_for(p.n * (2 * slot_words + 1), 8 * kOneThreads, 255);
+  if (per <= 4) seg_one<4><<<grid, kOneThreads, 0, s>>>(p, ws, alpha, grad_scale, slot_words, kl, per);
+  else seg_one<kOneMax><<<grid, kOneThreads, 0, s>>>(p, ws, alpha, grad_scale, slot_words, kl, per);
   return hipGetLastError();
 }
 

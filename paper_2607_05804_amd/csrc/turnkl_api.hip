@@ -265,6 +265,14 @@ void* scratch_address() {
   return g_scratch_ptr[dev];
 }
 
+// Segments and weights (a1, a2).
+hipError_t launch_prologue(const SegParams& sp, const Ws& ws, long long nblk, double alpha, float grad_scale,
+                           int n_chunks, float* kl, hipStream_t s) {
+  if (one_workgroup(sp)) return launch_one_workgroup(sp, ws, alpha, grad_scale, n_chunks, kl, s);
+  if (hipError_t e = launch_segments(sp, ws, nblk, s); e != hipSuccess) return e;
+  return launch_weights(sp, ws, alpha, grad_scale, n_chunks, kl, s);
+}
+
 // The fused call on a given workspace.  noalloc: the workspace is the scratch
 // array (its own size check and error code); status_out: optional device
 // int32 that receives the device-side status at the end of the call.
@@ -364,8 +372,7 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
   float* kl = token_kl_out ? token_kl_out : ws.kl;
 
   // ---- launches
-  if (launch_segments(sp, ws, L.nblk, stream) != hipSuccess) return TURNKL_ERR_HIP;
-  if (launch_weights(sp, ws, alpha, grad_scale, tiling.n_chunks, kl, stream) != hipSuccess)
+  if (launch_prologue(sp, ws, L.nblk, alpha, grad_scale, tiling.n_chunks, kl, stream) != hipSuccess)
     return TURNKL_ERR_HIP;
 
   RowParams rp{};
@@ -513,8 +520,8 @@ int turnkl_fwd_bwd_topk(const void* student_logits, int64_t ld_student, int dtyp
   float* kl = token_kl_out ? token_kl_out : ws.kl;
 
   // ---- launches
-  if (launch_segments(sp, ws, L.nblk, stream) != hipSuccess) return TURNKL_ERR_HIP;
-  if (launch_weights(sp, ws, alpha, grad_scale, 0, kl, stream) != hipSuccess) return TURNKL_ERR_HIP;
+  if (launch_prologue(sp, ws, L.nblk, alpha, grad_scale, 0, kl, stream) != hipSuccess)
+    return TURNKL_ERR_HIP;
   TopkParams tp{};
   tp.zs = student_logits;
   tp.ids = teacher_ids;

@@ -264,6 +264,10 @@ __device__ inline double turn_part(double alpha, const TurnTerm& u, double n_bt,
 hipError_t launch_segments(const SegParams& p, const Ws& ws, long long nblk, hipStream_t s);
 hipError_t launch_weights(const SegParams& p, const Ws& ws, double alpha, float grad_scale,
                           int n_chunks, float* kl, hipStream_t s);
+// Both in one kernel, for the batches that one_workgroup accepts.
+bool one_workgroup(const SegParams& p);
+hipError_t launch_one_workgroup(const SegParams& p, const Ws& ws, double alpha, float grad_scale,
+                                int n_chunks, float* kl, hipStream_t s);
 
 // Sizes are 32-bit here (the host rejects larger ones): the row kernel's
 // scalar registers are its scarcest resource.
