@@ -8,8 +8,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["turnkl_api.hip", "segment.hip", "rowkl.hip", "rowkl_ragged.hip", "reduce.hip", "topk.hip", "controller.cpp",
-           "diagnostics.cpp"]
+SOURCES = ["turnkl_api.hip", "segment.hip", "rowkl.hip", "rowkl_ragged.hip", "rowkl_whole.hip",
+           "reduce.hip", "topk.hip", "controller.cpp", "diagnostics.cpp"]
 LIB = os.path.join(HERE, "libturnkl.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,13 +30,13 @@ def _run(cmd, verbose: bool) -> None:
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    """Compile every source on its own, four at a time, and link them."""
+    """Compile every source on its own, eight at a time, and link them."""
     tmp = LIB + ".tmp"
     with tempfile.TemporaryDirectory() as d:
         objs = [os.path.join(d, s + ".o") for s in SOURCES]
         cmds = [[HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, s), "-o", o]
                 for s, o in zip(SOURCES, objs)]
-        with ThreadPoolExecutor(4) as pool:
+        with ThreadPoolExecutor(8) as pool:
             list(pool.map(lambda c: _run(c, verbose), cmds))
         _run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared", *extra, *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB)

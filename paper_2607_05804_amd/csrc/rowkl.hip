@@ -33,7 +33,14 @@
 // HBM, at 5.5 TB/s for 6,000 bf16 rows of 50,257 elements (2.0 TB/s with one
 // element per load) and 5.85 TB/s for 3,000 fp32 rows.
 //
-// Tasks are handed out by an atomic ticket in row-major order, so a
+// Rows of up to 2,048 packs take one workgroup each (kWhole, compiled in
+// rowkl_whole.hip), of one wave up to 512 packs, handed out by the hardware's
+// dispatch: their loads, sums and stores last less than the queue for the one
+// ticket counter.  What bounds them is latency below about 2,000 elements
+// (65,536 bf16 rows of 1,024: 94 us a call, 49 of them the other kernels), HBM
+// above (8,192: 4.9 TB/s over the whole call).
+//
+// Longer rows' tasks are handed out by an atomic ticket in row-major order, so a
 // workgroup only ever waits for tasks that running workgroups already hold
 // or that the next free workgroup will take; the wait is bounded and reports
 // TURNKL_ERR_SYNC_TIMEOUT instead of hanging.  An in-place gradient is safe
@@ -57,11 +64,12 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kRowWaves = kRowThreads / kWave;
 // Reference magnitude (log2 units, i.e. logits times log2 e) above which a
 // chunk, and then its row, subtracts its references per element.  Below it
 // the fast path's error term, a few u |m_s - m_t|, stays under 1e-5.
 constexpr float kFar2 = 64.0f * kLog2e;
+// Workgroups of a launch with one workgroup per row; beyond, each takes several.
+constexpr int kWholeGrid = 1 << 22;
 
 // ---------------------------------------------------------------------------
 // packs of kEpv elements moved with one load/store
@@ -334,28 +342,37 @@ __device__ inline unsigned own_mask(unsigned bits, int j) {
 //  kScalar:  one element per pack (rows shorter than a 16-byte pack).
 enum RowForm { kAligned, kRagged, kScalar };
 
-// One (row, chunk) task per iteration.  A chunk is the pack range
-// [pack_lo, pack_hi) of the row; thread tid owns packs pack_lo + v * 256 + tid
-// for v < kVpt.  The host's tiling makes every chunk at least 256 (kVpt - 1)
-// packs long, so every pack v < kVpt - 1 lies inside the chunk and only the
+// One (row, chunk) task per iteration (kWhole: one row, the whole of it, with
+// rows blockIdx.x, blockIdx.x + gridDim.x, ...).  A chunk is the pack range
+// [pack_lo, pack_hi) of the row; thread tid owns packs pack_lo + v * kThreads +
+// tid for v < kVpt.  The host's tiling makes every chunk at least kThreads
+// (kVpt - 1) packs long, so every pack v < kVpt - 1 lies inside the chunk and only the
 // last one is predicated (kScalar: all of them; kRagged: the first and the
 // last one, which may stick out of the row).
-template <bool kBf16, int kEpv, int kVpt, RowForm kForm, bool kSplit>
-__global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
+template <bool kBf16, int kEpv, int kVpt, RowForm kForm, bool kSplit, int kThreads, bool kWhole>
+__global__ __launch_bounds__(kThreads) void rowkl_kernel(RowParams p) {
   constexpr bool kCheckAll = kForm == kScalar;
+  // sums taken pack by pack: one more operation in eight, and an error against
+  // 64 bits below that of a chain over all of a thread's elements
+  constexpr bool kPackSums = kWhole || kForm == kRagged;
   using P = Pack<kBf16, kEpv>;
   constexpr int kEs = kBf16 ? 2 : 4;
   constexpr int kPackBytes = kEpv * kEs;
-  constexpr int kStep = kRowThreads * kPackBytes;  // bytes between a thread's packs
+  constexpr int kWaves = kThreads / kWave;
+  constexpr int kChunkSlots = kWhole ? 1 : kMaxChunks;
+  constexpr int kStep = kThreads * kPackBytes;  // bytes between a thread's packs
 
-  __shared__ float s_max[2][kRowWaves];
-  __shared__ float s_sum[3][kRowWaves];
-  __shared__ unsigned long long s_word[kMaxChunks * kExchangeWords];
-  __shared__ float s_ref[kRowWaves];
-  __shared__ int s_lo[kMaxChunks + 1];  // first pack of each chunk
+  __shared__ float s_max[2][kWaves];
+  __shared__ float s_sum[3][kWaves];
+  __shared__ unsigned long long s_word[kChunkSlots * kExchangeWords];
+  __shared__ float s_ref[kWaves];
+  __shared__ int s_lo[kChunkSlots + 1];  // first pack of each chunk
   __shared__ unsigned s_task;
   __shared__ int s_timeout;
 
+  // kWhole: the first row's mask is on its way while the error key is awaited
+  unsigned my_row = blockIdx.x;
+  const unsigned char first_mask = kWhole ? p.mask[my_row] : 0;
   if (p.hdr->err_key != kNoError) return;
   // Two launches, one per load order (see the loads below): the split order
   // runs when at most 90% of the rows are supervised, the other one exits
@@ -368,7 +385,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
   const int wid = tid / kWave;
   const unsigned n_tasks = (unsigned)p.n_rows * (unsigned)p.n_chunks;
   // chunk c is packs [chunk_start(c), chunk_start(c + 1)) of the row
-  for (int k = tid; k <= p.n_chunks; k += kRowThreads)
+  for (int k = tid; !kWhole && k <= p.n_chunks; k += kThreads)
     s_lo[k] = (int)chunk_start(p.n_packs, p.n_chunks, p.align, k);
   // data of this wave's most recent 16-byte store, kept live until the next
   // task's loads are issued (see keep_alive)
@@ -388,26 +405,28 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
   unsigned next_task = kNoTicket;
 
   for (;;) {
-    if (tid == 0) {
+    if (!kWhole && tid == 0) {
       s_task = next_task != kNoTicket ? next_task : take_ticket(&p.hdr->ticket);
       next_task = kNoTicket;
     }
-    __syncthreads();
+    if (!kWhole || my_row != blockIdx.x) __syncthreads();
     // Wave priority follows the task's progress: issuing loads 0, partial
     // sums 1, gradient (or zero) stores 2.  A wave further along its task
     // wins the SIMD's issue arbitration, finishes its stores sooner and
     // starts its next loads sooner; this measured 3.5% faster than equal
     // priorities (6.97 against 7.23 ms for 65,536 rows, same process).
     __builtin_amdgcn_s_setprio(0);
-    const unsigned task = __builtin_amdgcn_readfirstlane(s_task);  // uniform: keep it scalar
+    // uniform: keep it scalar
+    const unsigned task = kWhole ? my_row : __builtin_amdgcn_readfirstlane(s_task);
+    my_row += gridDim.x;
     if (task >= n_tasks) break;
     // s_task is rewritten only after every wave has passed a later barrier of
     // this task (pass 1's, or the masked path's), so no wave can miss it
-    if (tid == 0) s_timeout = 0;
-    const long long row = (long long)(task / (unsigned)p.n_chunks);
-    const int c = (int)(task - (unsigned)row * (unsigned)p.n_chunks);
-    const int pack_lo = __builtin_amdgcn_readfirstlane(s_lo[c]);
-    int pack_hi = __builtin_amdgcn_readfirstlane(s_lo[c + 1]);
+    if (!kWhole && tid == 0) s_timeout = 0;
+    const long long row = kWhole ? task : (long long)(task / (unsigned)p.n_chunks);
+    const int c = kWhole ? 0 : (int)(task - (unsigned)row * (unsigned)p.n_chunks);
+    const int pack_lo = kWhole ? 0 : __builtin_amdgcn_readfirstlane(s_lo[c]);
+    int pack_hi = kWhole ? p.n_packs : __builtin_amdgcn_readfirstlane(s_lo[c + 1]);
     long long col = (long long)pack_lo * kEpv;  // first element of the chunk
     const int lane_off = tid * kPackBytes;
     // Ragged rows: the row's first pack begins pre / kEs elements before the
@@ -427,11 +446,11 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       col -= pre / kEs;
       const int n = pack_hi - pack_lo;
       const int e_first = (int)col + tid * kEpv;
-      const int e_last = e_first + (kVpt - 1) * kRowThreads * kEpv;
+      const int e_last = e_first + (kVpt - 1) * kThreads * kEpv;
       const int at_first = inside_row(e_first, p.vocab - kEpv);
       const int at_last = inside_row(e_last, p.vocab - kEpv);
       bits_first = tid < n ? own_bits<kEpv>(e_first - at_first) : 0u;
-      bits_last = (kVpt - 1) * kRowThreads + tid < n ? own_bits<kEpv>(e_last - at_last) : 0u;
+      bits_last = (kVpt - 1) * kThreads + tid < n ? own_bits<kEpv>(e_last - at_last) : 0u;
       off_first = (at_first - (int)col) * kEs;
       off_last = (at_last - (int)col) * kEs;
     }
@@ -443,14 +462,14 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       if (kForm == kRagged)
         valid[v] = v == 0 ? bits_first != 0u : (v == kVpt - 1 ? bits_last != 0u : true);
       else
-        valid[v] = (kCheckAll || v == kVpt - 1) ? (v * kRowThreads + tid < n_valid) : true;
+        valid[v] = (kCheckAll || v == kVpt - 1) ? (v * kThreads + tid < n_valid) : true;
     }
     // the offsets of pack v's loads and stores: per-lane part and uniform part
 #define TURNKL_EDGE(v) (kForm == kRagged && ((v) == 0 || (v) == kVpt - 1))
 #define TURNKL_OFF_V(v) (TURNKL_EDGE(v) ? ((v) == 0 ? off_first : off_last) : lane_off)
 #define TURNKL_OFF_S(v) (TURNKL_EDGE(v) ? 0 : (v) * kStep)
 
-    if (!p.mask[row]) {
+    if (!(kWhole && task == blockIdx.x ? first_mask : p.mask[row])) {
       if (p.lse && c == 0 && tid == 0) {  // the row is not read: no log-partition function
         p.lse[2 * row] = __builtin_nanf("");
         p.lse[2 * row + 1] = __builtin_nanf("");
@@ -463,12 +482,12 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         for (int v = 0; v < kVpt; ++v)
           if (valid[v]) P::store(rg, TURNKL_OFF_V(v), TURNKL_OFF_S(v), z);
         __builtin_amdgcn_s_setprio(0);
-        if (tid == 0) next_task = take_ticket(&p.hdr->ticket);
+        if (!kWhole && tid == 0) next_task = take_ticket(&p.hdr->ticket);
         // the zeros sit in registers the loop's phi copies may take over
         // right away: let the stores complete first
         drain_stores();
         keep_alive(carry);
-      } else if (tid == 0) {
+      } else if (!kWhole && tid == 0) {
         next_task = take_ticket(&p.hdr->ticket);
       }
       __syncthreads();
@@ -536,7 +555,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     __syncthreads();                                     \
     MS = s_max[0][0];                                    \
     MT = s_max[1][0];                                    \
-    _Pragma("unroll") for (int w = 1; w < kRowWaves; ++w) { \
+    _Pragma("unroll") for (int w = 1; w < kWaves; ++w) { \
       MS = fmaxf(MS, s_max[0][w]);                       \
       MT = fmaxf(MT, s_max[1][w]);                       \
     }                                                    \
@@ -560,7 +579,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     SS = s_sum[0][0];                                                         \
     AA = s_sum[1][0];                                                         \
     ST = s_sum[2][0];                                                         \
-    _Pragma("unroll") for (int w = 1; w < kRowWaves; ++w) {                   \
+    _Pragma("unroll") for (int w = 1; w < kWaves; ++w) {                   \
       SS += s_sum[0][w];                                                      \
       AA += s_sum[1][w];                                                      \
       ST += s_sum[2][w];                                                      \
@@ -575,6 +594,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     AA = 0.0f;                                                                \
     ST = 0.0f;                                                                \
     _Pragma("unroll") for (int v = 0; v < kVpt; ++v) {                        \
+      float ps = 0.0f, pa = 0.0f, pt = 0.0f;                                  \
       _Pragma("unroll") for (int j = 0; j < kEpv; ++j) {                      \
         const float a = xs[v].get(j);                                         \
         const float b = xt[v].get(j);                                         \
@@ -598,9 +618,20 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
           et = valid[v] ? et : 0.0f;                                          \
           d = valid[v] ? d : 0.0f;                                            \
         }                                                                     \
-        SS += es;                                                             \
-        AA = fmaf(es, d, AA);                                                 \
-        ST += et;                                                             \
+        if (kPackSums) {                                                      \
+          ps = j ? ps + es : es;                                              \
+          pa = j ? fmaf(es, d, pa) : es * d;                                  \
+          pt = j ? pt + et : et;                                              \
+        } else {                                                              \
+          SS += es;                                                           \
+          AA = fmaf(es, d, AA);                                               \
+          ST += et;                                                           \
+        }                                                                     \
+      }                                                                       \
+      if (kPackSums) {                                                        \
+        SS += ps;                                                             \
+        AA += pa;                                                             \
+        ST += pt;                                                             \
       }                                                                       \
       /* keeps the compiler from taking one sum over all packs at a time,     \
          with every unpacked value alive: over 200 more VGPRs */              \
@@ -610,10 +641,15 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
   }
 
     float ms = -INFINITY, mt = -INFINITY;
+    // (one wave takes the maximum over all packs: over the first ones alone its
+    // sample would be a quarter of what a chunk's usually is)
 #pragma unroll
-    for (int j = 0; j < kEpv; ++j) {
-      ms = fmaxf(ms, valid[0] ? xs[0].get(j) : -INFINITY);
-      mt = fmaxf(mt, valid[0] ? xt[0].get(j) : -INFINITY);
+    for (int v = 0; v < (kThreads == kWave ? kVpt : 1); ++v) {
+#pragma unroll
+      for (int j = 0; j < kEpv; ++j) {
+        ms = fmaxf(ms, valid[v] ? xs[v].get(j) : -INFINITY);
+        mt = fmaxf(mt, valid[v] ? xt[v].get(j) : -INFINITY);
+      }
     }
     TURNKL_BLOCK_MAX2(ms, mt)
     float m2s = ms * kLog2e;
@@ -638,9 +674,9 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         // path costs the ragged kernel over 100 VGPRs.  (A moved pack's
         // foreign elements are the row's own too, so any may be the maximum.)
 #pragma unroll 1
-        for (int v = 0; v < kVpt && v * kRowThreads + tid < n_valid; ++v) {
+        for (int v = 0; v < kVpt && v * kThreads + tid < n_valid; ++v) {
           P ya, yb;
-          const int off = (inside_row((int)col + (v * kRowThreads + tid) * kEpv, p.vocab - kEpv) - (int)col) * kEs;
+          const int off = (inside_row((int)col + (v * kThreads + tid) * kEpv, p.vocab - kEpv) - (int)col) * kEs;
           ya.load(rs, off, 0);
           yb.load(rt, off, 0);
 #pragma unroll
@@ -686,7 +722,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       mt = s_max[1][0];
       bm = s_ref[0];
 #pragma unroll
-      for (int w = 1; w < kRowWaves; ++w) {
+      for (int w = 1; w < kWaves; ++w) {
         const float oa = s_max[0][w];
         const float ob = s_ref[w];
         const bool take = (oa > ms) | ((oa == ms) & (ob > bm));
@@ -706,9 +742,9 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         aa = 0.0f;
         st = 0.0f;
 #pragma unroll 1
-        for (int v = 0; v < kVpt && v * kRowThreads + tid < n_valid; ++v) {
+        for (int v = 0; v < kVpt && v * kThreads + tid < n_valid; ++v) {
           P ya, yb;
-          const int e = (int)col + (v * kRowThreads + tid) * kEpv;
+          const int e = (int)col + (v * kThreads + tid) * kEpv;
           const int at = inside_row(e, p.vocab - kEpv);
           const unsigned bits = own_bits<kEpv>(e - at);
           ya.load(rs, (at - (int)col) * kEs, 0);
@@ -750,7 +786,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
     float r_s, r_t;              // row references of the exponents, logit units
     float d_s = 0.0f, d_t = 0.0f;  // row reference C* of the difference a - b
     bool row_offset = offset;
-    if (p.n_chunks > 1) {
+    if (!kWhole && p.n_chunks > 1) {
       const int nw = p.n_chunks * kExchangeWords;
       unsigned long long* slot = p.slots + row * (long long)nw;
       if (tid == 0) {
@@ -766,7 +802,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       // Wait for every word of the row, bounded: after spin_limit empty polls,
       // or as soon as another workgroup of the call has timed out (checked
       // every 256 polls), the task ends with the timeout error.
-      for (int q = tid; q < nw; q += kRowThreads) {
+      for (int q = tid; q < nw; q += kThreads) {
         unsigned long long x;
         int spins = 0;
         while ((x = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {
@@ -836,7 +872,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
       merge_chunk(offset, w, r_s, r_t, two_diff(d_s, d_t), r);
     }
     // without a gradient to write the task ends here
-    if (tid == 0 && !p.grad) next_task = take_ticket(&p.hdr->ticket);
+    if (!kWhole && tid == 0 && !p.grad) next_task = take_ticket(&p.hdr->ticket);
 
     // mu = <p_s, (a - b) - (C*_a - C*_b)>,
     // KL = <p_s, a - b> - lse(a) + lse(b) = mu + ((C*_a - R_s) - (C*_b - R_t)) + ln(S_t / S_s)
@@ -880,7 +916,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
           __builtin_amdgcn_sched_barrier(0);
           keep_alive(prev);
           prev = cur;
-          if (v == kVpt - 1 && tid == 0) next_task = take_ticket(&p.hdr->ticket);
+          if (!kWhole && v == kVpt - 1 && tid == 0) next_task = take_ticket(&p.hdr->ticket);
         }
         carry = prev;
         __builtin_amdgcn_s_setprio(0);
@@ -896,14 +932,14 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
         keep_alive(carry);
 #pragma unroll 1
         for (int v = 0; v < kVpt; ++v) {
-          if (v * kRowThreads + tid >= n_valid) break;
+          if (v * kThreads + tid >= n_valid) break;
           P ya, yb;
           // a ragged row's pack that sticks out of the row: only its own
           // elements are written, since a neighbour may have overwritten the
           // shared ones (in place) before this pack was read
           int shift = 0, off = lane_off + v * kStep;
           if constexpr (kForm == kRagged) {
-            const int e = (int)col + (v * kRowThreads + tid) * kEpv;
+            const int e = (int)col + (v * kThreads + tid) * kEpv;
             const int at = inside_row(e, p.vocab - kEpv);
             shift = e - at;
             off = (at - (int)col) * kEs;
@@ -939,6 +975,7 @@ __global__ __launch_bounds__(kRowThreads) void rowkl_kernel(RowParams p) {
 // ---------------------------------------------------------------------------
 // launch
 
+#ifndef TURNKL_WHOLE_ROWS
 int cu_count() {
   static int cache[64] = {0};
   int dev = 0;
@@ -974,7 +1011,7 @@ hipError_t launch_tasks(const RowParams& p, hipStream_t s) {
 
 template <bool kBf16, int kEpv, int kVpt, RowForm kForm, bool kSplit = false>
 hipError_t launch_one(const RowParams& p, hipStream_t s) {
-  return launch_tasks<rowkl_kernel<kBf16, kEpv, kVpt, kForm, kSplit>>(p, s);
+  return launch_tasks<rowkl_kernel<kBf16, kEpv, kVpt, kForm, kSplit, kRowThreads, false>>(p, s);
 }
 
 #ifndef TURNKL_RAGGED_ROWS
@@ -1008,8 +1045,11 @@ hipError_t launch_vpt(const RowParams& p, int vpt, hipStream_t s) {
   switch (vpt) {
 #define TURNKL_CASE(n) \
     case n: return launch_vector<kBf16, kEpv, n>(p, s);
+#ifndef TURNKL_RAGGED_ROWS  // shorter ragged rows take one workgroup each
     TURNKL_CASE(1) TURNKL_CASE(2) TURNKL_CASE(3) TURNKL_CASE(4) TURNKL_CASE(5) TURNKL_CASE(6)
-    TURNKL_CASE(7) TURNKL_CASE(8) TURNKL_CASE(9) TURNKL_CASE(10) TURNKL_CASE(11) TURNKL_CASE(12)
+    TURNKL_CASE(7)
+#endif
+    TURNKL_CASE(8) TURNKL_CASE(9) TURNKL_CASE(10) TURNKL_CASE(11) TURNKL_CASE(12)
     TURNKL_CASE(13) TURNKL_CASE(14) TURNKL_CASE(15) TURNKL_CASE(16) TURNKL_CASE(17) TURNKL_CASE(18)
     TURNKL_CASE(19) TURNKL_CASE(20) TURNKL_CASE(21) TURNKL_CASE(22)
 #ifndef TURNKL_RAGGED_ROWS
@@ -1020,11 +1060,42 @@ hipError_t launch_vpt(const RowParams& p, int vpt, hipStream_t s) {
   }
 }
 
+#else
+template <bool kBf16, int kEpv, int kVpt, RowForm kForm, int kThreads>
+hipError_t launch_whole(const RowParams& p, hipStream_t s) {
+  constexpr bool kSplit = kBf16 && kForm == kAligned;
+  const int grid = p.n_rows < kWholeGrid ? p.n_rows : kWholeGrid;
+  rowkl_kernel<kBf16, kEpv, kVpt, kForm, kSplit, kThreads, true><<<grid, kThreads, 0, s>>>(p);
+  return hipGetLastError();
+}
+
+template <bool kBf16, int kEpv, RowForm kForm>
+hipError_t launch_whole_vpt(const RowParams& p, const RowTiling& t, hipStream_t s) {
+  switch (t.threads * 32 + t.vpt) {
+#define TURNKL_CASE(threads, n) \
+    case threads * 32 + n: return launch_whole<kBf16, kEpv, n, kForm, threads>(p, s);
+    TURNKL_CASE(64, 1) TURNKL_CASE(64, 2) TURNKL_CASE(64, 3) TURNKL_CASE(64, 4) TURNKL_CASE(64, 5)
+    TURNKL_CASE(64, 6) TURNKL_CASE(64, 7) TURNKL_CASE(64, 8)
+    TURNKL_CASE(256, 3) TURNKL_CASE(256, 4) TURNKL_CASE(256, 5) TURNKL_CASE(256, 6) TURNKL_CASE(256, 7)
+    TURNKL_CASE(256, 8)
+#undef TURNKL_CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+#endif
+
 }  // namespace
 
-#ifndef TURNKL_RAGGED_ROWS
+#if defined(TURNKL_WHOLE_ROWS)
+hipError_t launch_whole_rows(const RowParams& p, const RowTiling& t, hipStream_t s) {
+  if (t.ragged)
+    return p.bf16 ? launch_whole_vpt<true, 8, kRagged>(p, t, s) : launch_whole_vpt<false, 4, kRagged>(p, t, s);
+  return p.bf16 ? launch_whole_vpt<true, 8, kAligned>(p, t, s) : launch_whole_vpt<false, 4, kAligned>(p, t, s);
+}
+#elif !defined(TURNKL_RAGGED_ROWS)
 hipError_t launch_rows(const RowParams& p, const RowTiling& t, hipStream_t s) {
   if (p.n_rows == 0) return hipSuccess;
+  if (t.threads) return launch_whole_rows(p, t, s);
   if (t.ragged) return launch_ragged_rows(p, t, s);
   if (!t.vector) {
     return p.bf16 ? launch_one<true, 1, kScalarVpt, kScalar>(p, s)

@@ -130,6 +130,47 @@ RowTiling ragged_tiling(long long vocab, int dtype, uintptr_t start, long long s
   return t;  // not reached: the last grid with align = 1 always fits
 }
 
+// Short rows take one workgroup each, without tickets: every ticket is an
+// atomic on one address, 12.3 ns, which the tasks of all CUs queue for (65,536
+// bf16 rows of 1,024: 808 us a call, 94 without; of 8,192: 837, 436).  Up to
+// kWavePacks packs the workgroup is one wave, without barriers (3,001: 253 us with
+// 256 threads, 200 with 64).  Past kWholePacks the rows last longer than the
+// tickets, and workgroups that go on from row to row keep the stores in a
+// narrower window of addresses: 65,536 rows of 24,000 take 1,282 us here, 1,180
+// with tickets; of 16,384: 888, 918.
+// A ragged row needs every pack but a thread's first and last inside it, for
+// every start (see ragged_tiling).
+constexpr int kWavePacks = 512;
+constexpr int kWholePacks = 2048;
+
+RowTiling whole_tiling(long long vocab, int dtype, bool ragged, uintptr_t start, long long stride) {
+  RowTiling t{};
+  t.vector = !ragged;
+  t.ragged = ragged;
+  t.epv = dtype == TURNKL_BF16 ? 8 : 4;
+  t.n_chunks = 1;
+  t.align = 1;
+  const long long bytes = vocab * (16 / t.epv);
+  for (int mask : {127, 0}) {
+    const bool one_start = !ragged || stride % 128 == 0 || mask == 0;
+    const long long pre = ragged ? (long long)(start & (uintptr_t)mask) : 0;
+    const long long most = ceil_div((one_start ? pre : mask) + bytes, 16);
+    const long long least = ceil_div((one_start ? pre : 0) + bytes, 16);
+    if (most > kWholePacks) return t;
+    const int threads = most <= kWavePacks ? 64 : kRowThreads;
+    const int vpt = (int)ceil_div(most, threads);
+    if (ragged && least - 1 < (long long)threads * (vpt - 1)) continue;
+    t.threads = threads;
+    t.vpt = vpt;
+    t.line_mask = mask;
+    t.packs = most;
+    t.chunk = most * t.epv;
+    t.min_chunk = most;
+    return t;
+  }
+  return t;  // not reached: the second grid always fits
+}
+
 namespace {
 
 // Whether a vocabulary admits the vector path at all (whole 16-byte packs, and
@@ -325,6 +366,8 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
     bool ok = vector_possible(tiling, vocab) && ld_student % epv == 0 && ld_teacher % epv == 0;
     ok = ok && ((uintptr_t)student_logits & 15u) == 0 && ((uintptr_t)teacher_logits & 15u) == 0;
     if (grad_out) ok = ok && ld_grad % epv == 0 && ((uintptr_t)grad_out & 15u) == 0;
+    const uintptr_t lines = (uintptr_t)(grad_out ? grad_out : student_logits);
+    const long long stride = (long long)(grad_out ? ld_grad : ld_student) * (long long)es;
     // Other rows take the 16-byte loads of the ragged path, down to one pack
     // per row: at V = 50,257 the whole call takes 280 us for 6,000 bf16 rows
     // packed without padding (element-wise path: 724 us) and 265 us for 3,000
@@ -335,9 +378,16 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
         // the limits below and the workspace stay those of the element-wise
         // path, which has at least as many chunks
         slot_chunks = tiling.n_chunks;
-        const void* lines = grad_out ? grad_out : student_logits;
-        tiling = ragged_tiling(vocab, dtype, (uintptr_t)lines,
-                               (long long)(grad_out ? ld_grad : ld_student) * (long long)es);
+        tiling = ragged_tiling(vocab, dtype, lines, stride);
+      }
+    }
+    // Short rows: one workgroup each (a tiling override keeps whole packs on
+    // the chunks that it asks for).
+    if (vocab >= epv && (!ok || t_vpt_override == 0)) {
+      const RowTiling w = whole_tiling(vocab, dtype, !ok, lines, stride);
+      if (w.threads) {
+        if (slot_chunks == 0) slot_chunks = tiling.n_chunks;
+        tiling = w;
       }
     }
   }

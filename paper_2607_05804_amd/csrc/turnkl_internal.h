@@ -193,6 +193,7 @@ struct RowTiling {
   bool ragged;      // 16-byte vectors on rows of any start and length (>= one vector)
   int line_mask;    // ragged: the packs' grid starts at a row's address & ~line_mask
   long long packs;  // ragged: packs of a row at most
+  int threads;      // one workgroup of this size per row (vpt packs a thread); 0: chunks and tickets
 };
 
 // First pack of chunk c (0 <= c <= n_chunks) of a row of n_packs packs: the
@@ -215,6 +216,9 @@ RowTiling scalar_tiling(long long vocab);
 // Tiling of the ragged path; `start` and `stride` are the address and the row
 // stride in bytes of the matrix whose lines the packs follow.
 RowTiling ragged_tiling(long long vocab, int dtype, uintptr_t start, long long stride);
+// Tiling of short rows, one workgroup each (threads == 0: the row is not
+// short).  ragged: by `start` and `stride` as above, else rows of whole packs.
+RowTiling whole_tiling(long long vocab, int dtype, bool ragged, uintptr_t start, long long stride);
 
 // ---------------------------------------------------------------------------
 // launches (each returns hipSuccess or the launch error)
@@ -302,6 +306,7 @@ constexpr int kDefaultSpinLimit = 1 << 22;
 
 hipError_t launch_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 hipError_t launch_ragged_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
+hipError_t launch_whole_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 
 // Top-K path (the teacher's top-K support; both distributions renormalised on
 // it).  The row kernel writes each supervised row's scaled gradient on the

@@ -45,6 +45,10 @@ CASES = [
     (2049, "bf16", (0, 63), (0, 63), (0, 63), "new", 0.0),    # one element past 256 packs, rows on lines
     (4097, "bf16", (2, 0), (0, 5), (1, 7), "new", 0.0),
     (1001, "f32", (0, 0), (0, 0), (0, 0), "forward", 0.0),
+    (4030, "bf16", (0, 0), (1, 0), (0, 0), "new", 0.0),       # one wave or 256 threads, by the row's start
+    (2023, "f32", (3, 0), (3, 0), (3, 0), "inplace", 800.0),
+    (16319, "bf16", (0, 0), (0, 0), (5, 0), "new", 0.0),      # the longest rows with a workgroup each
+    (16321, "bf16", (0, 0), (0, 0), (5, 0), "inplace", 0.0),  # chunks
     (45057, "bf16", (0, 0), (0, 0), (0, 0), "inplace", 0.0),  # one element past the widest chunk
     (50257, "bf16", (0, 0), (0, 0), (0, 0), "new", 0.0),
     (50257, "f32", (0, 47), (0, 47), (0, 47), "new", 0.0),
