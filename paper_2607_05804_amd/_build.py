@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = ["turnkl_api.hip", "segment.hip", "rowkl.hip", "rowkl_ragged.hip", "rowkl_whole.hip",
-           "reduce.hip", "topk.hip", "controller.cpp", "diagnostics.cpp"]
+           "rowfwd.hip", "reduce.hip", "topk.hip", "controller.cpp", "diagnostics.cpp"]
 LIB = os.path.join(HERE, "libturnkl.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -307,6 +307,7 @@ constexpr int kDefaultSpinLimit = 1 << 22;
 hipError_t launch_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 hipError_t launch_ragged_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 hipError_t launch_whole_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
+hipError_t launch_forward_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 
 // Top-K path (the teacher's top-K support; both distributions renormalised on
 // it).  The row kernel writes each supervised row's scaled gradient on the

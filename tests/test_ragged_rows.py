@@ -1,6 +1,7 @@
 """The row kernel for rows of any start and length, on the CPU: its generated
 code, and the packs its index arithmetic gives each row."""
 import os
+import re
 import subprocess
 
 import numpy as np
@@ -13,6 +14,7 @@ from test_compiler_guards import CSRC, FLAGS, HIPCC, ROOT, kernel_budgets, store
 @pytest.mark.parametrize("source,kernels", [
     ("rowkl_ragged.hip", 2 * 15),          # packs per thread x dtypes
     ("rowkl_whole.hip", 2 * 2 * (8 + 6)),  # also: whole packs or any start and length
+    ("rowfwd.hip", 2 * 2),
 ])
 def test_generated_code(source, kernels, tmp_path):
     """Every instantiation within 256 VGPRs, no AGPRs, no scratch, no store data
@@ -23,7 +25,7 @@ def test_generated_code(source, kernels, tmp_path):
     subprocess.run([HIPCC, *FLAGS, os.path.join(CSRC, source), "-o", str(out)],
                    check=True, capture_output=True, timeout=900)
     asm = out.read_text()
-    rows = [b for b in kernel_budgets(asm) if "rowkl_kernel" in b[0]]
+    rows = [b for b in kernel_budgets(asm) if re.search("rowkl_kernel|rowfwd_kernel", b[0])]
     assert len(rows) == kernels
     bad = [b for b in rows if b[1] > 256 or b[2] > 0 or b[3] > 0]
     assert not bad, bad
