@@ -24,6 +24,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 ROW_KERNEL_SOURCES = ["paper_2607_05804_amd/csrc/rowkl.hip",
+                      "paper_2607_05804_amd/csrc/row_ops.h",
                       "paper_2607_05804_amd/csrc/turnkl_internal.h",
                       "paper_2607_05804_amd/csrc/block_ops.h"]
 COUNTER_FILE = os.path.join(ROOT, "profiles", "rowkl_long_horizon_counters.md")

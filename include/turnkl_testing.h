@@ -34,8 +34,10 @@ int turnkl_profile_row_kernel(hipEvent_t before, hipEvent_t after);
  * n = vectors_per_thread is the most vectors a thread holds (1 to 25; default
  * 25).  Smaller n means more, smaller chunks per row, hence more exchange
  * slots: size the workspace with turnkl_testing_workspace_bytes for the same
- * n.  0 restores the default.  Results agree up to floating-point summation
- * order.  Returns TURNKL_ERR_INVALID_ARG for values outside 0..25.
+ * n.  0 restores the default, under which rows of up to 2,048 vectors take one
+ * workgroup each instead.  Rows that are no whole vectors, or do not start on
+ * one, are tiled on their own and ignore the setting.  Results agree up to
+ * floating-point summation order.  Returns TURNKL_ERR_INVALID_ARG for values outside 0..25.
  */
 int turnkl_set_row_tiling(int vectors_per_thread);
 
@@ -47,8 +49,8 @@ size_t turnkl_testing_workspace_bytes(int64_t n_tokens, int64_t vocab, int dtype
                                       int vectors_per_thread);
 
 /*
- * Bound on the row kernel's wait for the partials of a row's other chunks: a
- * workgroup gives up after this many polls that find a partial missing,
+ * Bound on the row kernel's wait for the partials of a row's other chunks (a
+ * call without a gradient never waits): a workgroup gives up after this many polls that find a partial missing,
  * records TURNKL_ERR_SYNC_TIMEOUT in the workspace and exits; the other
  * workgroups that wait give up within 256 polls of their own wait, and the
  * later kernels of the call see the error and skip their work.  0
