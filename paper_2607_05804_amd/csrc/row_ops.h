@@ -216,14 +216,17 @@ constexpr unsigned kNoErrorLow = 0xFFFFFFFFu;
 // other term, and a peaked row's KL does not come from cancelling terms.
 // The row works against natural references (R_s, R_t) >= every chunk's
 // reference and the difference reference C* of the offset chunk with the
-// largest C_a ((0, 0) when all chunks are fast), and accumulates in chunk order
+// largest C_a, or (0, 0) where a fast chunk's reference lies above that (all
+// chunks fast; or the offset ones hold masked logits, whose difference from the
+// teacher's may be of any size), and accumulates in chunk order
 //   S_s = sum_v 2^((a_v - R_s) log2e),  S_t likewise,
 //   A   = sum_v 2^((a_v - R_s) log2e) ((a_v - b_v) - (C*_a - C*_b)),
 // so that KL = A / S_s + ((C*_a - R_s) - (C*_b - R_t)) + ln(S_t / S_s).
 // A fast chunk scales by 2^(M_s - R_s log2e) (one FMA for the exponent), an
 // offset chunk by 2^((M_s - R_s) log2e); both add
 // S_s ((C_a - C_b) - (C*_a - C*_b)) to A (exact differences), zero for rows of
-// fast chunks only.
+// fast chunks only.  Where the scale is zero the chunk adds nothing to A: its
+// own A, and S_s times the difference of the references, may be infinite.
 struct RowSums {
   float ss, aa, st;
 };
@@ -263,7 +266,7 @@ __device__ inline void merge_chunk(bool offset, const float* w, float rs, float 
   }
   const float aa = fmaf(w[1], diff_minus(w[5], w[6], c_row), w[2]);
   r.ss = fmaf(w[1], fs, r.ss);
-  r.aa = fmaf(aa, fs, r.aa);
+  r.aa = fs == 0.0f ? r.aa : fmaf(aa, fs, r.aa);
   r.st = fmaf(w[4], ft, r.st);
 }
 

@@ -194,10 +194,11 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
         }
         const Float2 c2 = two_diff(ca, cb);
         if (na != ms || cb != c_b) {
+          // (f == 0, as for masked logits before the first others: the sums so
+          // far are dropped; aa, and ss times the difference, may be infinite)
           const float f = ms == -INFINITY ? 0.0f : exp2f((ms - na) * kLog2e);
-          aa = ss == 0.0f ? aa : fmaf(ss, diff_minus(c_a, c_b, c2), aa);
+          aa = f == 0.0f ? 0.0f : fmaf(ss, diff_minus(c_a, c_b, c2), aa) * f;
           ss *= f;
-          aa *= f;
           ms = na;
           c_a = ca;
           c_b = cb;
@@ -231,10 +232,9 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
         wb = take ? ob : wb;
       }
       const Float2 cw = two_diff(wa, wb);
-      const bool none = ms == -INFINITY;
-      const float fs = none ? 0.0f : exp2f((ms - wa) * kLog2e);
+      const float fs = ms == -INFINITY ? 0.0f : exp2f((ms - wa) * kLog2e);
       const float ft = mt == -INFINITY ? 0.0f : exp2f((mt - wt) * kLog2e);
-      aa = (none ? aa : fmaf(ss, diff_minus(c_a, c_b, cw), aa)) * fs;
+      aa = fs == 0.0f ? 0.0f : fmaf(ss, diff_minus(c_a, c_b, cw), aa) * fs;
       ss = wave_sum(ss * fs);
       aa = wave_sum(aa);
       st = wave_sum(st * ft);
@@ -269,6 +269,10 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
           x[6] = s_part[w][6];
           any = true;
         }
+      }
+      if (x[5] < x[0]) {  // a wave in the fast form holds the chunk's reference
+        x[5] = 0.0f;
+        x[6] = 0.0f;
       }
       RowSums r{0.0f, 0.0f, 0.0f};
       const Float2 c2 = two_diff(x[5], x[6]);
@@ -342,6 +346,10 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
             } else {
               merge_chunk(o, w, r_s, r_t, two_diff(d_s, d_t), sum);
             }
+          }
+          if (d_s < r_s) {
+            d_s = 0.0f;
+            d_t = 0.0f;
           }
         }
         if (lane == 0) {

@@ -574,6 +574,10 @@ __global__ __launch_bounds__(kThreads) void rowkl_kernel(RowParams p) {
 #pragma unroll 1
       for (int k = kUnrolled; k < p.n_chunks; ++k) TURNKL_REFS(k)
 #undef TURNKL_REFS
+      if (d_s < r_s) {  // a fast chunk holds the row's reference
+        d_s = 0.0f;
+        d_t = 0.0f;
+      }
       const Float2 c_row = two_diff(d_s, d_t);
 #pragma unroll
       for (int k = 0; k < kUnrolled; ++k)
