@@ -23,6 +23,11 @@ constexpr float kLn2 = 0.6931471805599453f;
 // chunk, and then its row, subtracts its references per element.  Below it
 // the fast path's error term, a few u |m_s - m_t|, stays under 1e-5.
 constexpr float kFar2 = 64.0f * kLog2e;
+// Sums against sampled references above which a chunk (or wave) is redone
+// against its exact maxima: all of a row's chunks and waves, at most 512 of
+// them, then add up inside the float range.  The sum of 2^(..) (a - b) counts
+// too: it leaves the range a few units of logits before the sum of 2^(..).
+constexpr float kMaxSum = 0x1p118f;
 
 // ---------------------------------------------------------------------------
 // packs of kEpv elements moved with one load/store
@@ -230,6 +235,11 @@ constexpr unsigned kNoErrorLow = 0xFFFFFFFFu;
 struct RowSums {
   float ss, aa, st;
 };
+
+// whether a chunk's (or wave's) sums in the fast form may stand
+__device__ inline bool sums_in_range(float ss, float aa, float st) {
+  return ss + st + fabsf(aa) <= kMaxSum;  // false for NaN
+}
 
 // Error-free difference (Knuth's TwoSum applied to x + (-y)): hi = fl(x - y)
 // and hi + lo = x - y exactly.  Needs plain rounded adds, which this file

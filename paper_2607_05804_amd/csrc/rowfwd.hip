@@ -13,8 +13,8 @@
 // fp32: 436 and 197.
 //
 // Every wave sums its own packs against its own reference, the maximum of its
-// first four packs of each lane.  Where that is far from zero, or a sum
-// overflows, the wave goes over its packs in the offset form instead, every
+// first four packs of each lane.  Where that is far from zero, or a sum nears
+// an overflow, the wave goes over its packs in the offset form instead, every
 // lane with running maxima of its own, and the chunk is reported in that form.
 
 #include <type_traits>
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
       ss = wave_sum(ss);
       aa = wave_sum(aa);
       st = wave_sum(st);
-      offset = !(__builtin_isfinite(ss) && __builtin_isfinite(st));
+      offset = !sums_in_range(ss, aa, st);
     }
     if (offset && !idle) {
       // offset form: each lane against its own maxima so far, which it moves

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void rowkl_kernel(RowParams p) {
     // as long as no term overflows, so the fast path's reference is the
     // maximum over each thread's first pack only, folded into one FMA per
     // exponent (log2 units: the fast form of merge_chunk).  A chunk whose
-    // reference is far from zero (|max| > 64), or whose sums overflow, is
+    // reference is far from zero (|max| > 64), or whose sums near an overflow, is
     // redone against its exact maximum with the references subtracted per
     // element, directly in natural-reference form (uniform branch; cold for
     // ordinary logits).
@@ -386,8 +386,7 @@ __global__ __launch_bounds__(kThreads) void rowkl_kernel(RowParams p) {
     float ss, aa, st;
     float c_a = 0.0f, c_b = 0.0f;  // difference reference (offset form only)
     TURNKL_CHUNK_SUMS(false, m2s, m2t, Float2{}, ss, aa, st)
-    const bool offset = !(fmaxf(fabsf(m2s), fabsf(m2t)) <= kFar2) ||
-                        !(__builtin_isfinite(ss) && __builtin_isfinite(st));
+    const bool offset = !(fmaxf(fabsf(m2s), fabsf(m2t)) <= kFar2) || !sums_in_range(ss, aa, st);
     if (offset) {
       __syncthreads();  // s_max / s_sum are about to be reused
       TURNKL_FENCE_ALL()

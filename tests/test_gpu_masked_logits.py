@@ -1,5 +1,7 @@
-"""Rows with runs of very low logits (masked columns): every form of the row
-kernels, with and without a gradient; against the oracle."""
+"""Rows with runs of very low logits (masked columns), and rows with logits so far
+above the others that the sums against the sampled references come near the
+largest float: every form of the row kernels, with and without a gradient;
+against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -100,4 +102,26 @@ def test_masked_columns(V, dtype, ld, vpt, value, gpu):
                     t[run & (col % 2 == 0) if who == "half" else run] = low
                 zs.append(s)
                 zt.append(t)
+    _compare(np.stack(zs), np.stack(zt), dtype, ld, vpt)
+
+
+@pytest.mark.parametrize("V,dtype,ld,vpt", FORMS[:-1])
+def test_sums_near_the_largest_float(V, dtype, ld, vpt, gpu):
+    """Student logits 80 to 89 above the sampled references: the sum of
+    2^(..) (a - b) leaves the float range before the sum of 2^(..) does, and
+    sums that fit one by one overflow together."""
+    log(f"spikes V={V} {dtype} ld={ld} vpt={vpt}")
+    rng = np.random.default_rng(V)
+    zs, zt = [], []
+    for up in (80.0, 84.0, 85.0, 86.0, 87.0, 88.0, 88.5):
+        s = rng.normal(0, 3, V)
+        t = s + rng.normal(0, 1, V)
+        s[int(0.7 * V)] = s[:2048].max() + up
+        zs.append(s)
+        zt.append(t)
+        # the same value many times over, in every wave and chunk
+        s = np.zeros(V)
+        s[int(0.2 * V)::max(V // 40, 1)] = up
+        zs += [s, s]
+        zt += [rng.normal(0, 1, V), s + rng.normal(0, 1, V)]
     _compare(np.stack(zs), np.stack(zt), dtype, ld, vpt)
