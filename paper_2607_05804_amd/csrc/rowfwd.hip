@@ -306,8 +306,7 @@ __global__ __launch_bounds__(kFwdThreads, 6) void rowfwd_kernel(RowParams p) {
             __hip_atomic_store(slot + c * kExchangeWords + q, words[q], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
           drain_stores();  // the words are visible before the count
-          // the row's KL is zero until the last workgroup writes it
-          arrived = __hip_atomic_fetch_add(reinterpret_cast<unsigned*>(p.kl + row), 1u, __ATOMIC_RELAXED,
+          arrived = __hip_atomic_fetch_add(reinterpret_cast<unsigned*>(p.wsc + row), 1u, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
         }
         last = __builtin_amdgcn_readfirstlane(arrived) + 1u == (unsigned)p.n_chunks;

@@ -422,7 +422,12 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
   float* kl = token_kl_out ? token_kl_out : ws.kl;
 
   // ---- launches
-  if (launch_prologue(sp, ws, L.nblk, alpha, grad_scale, tiling.n_chunks, kl, stream) != hipSuccess)
+  // Without a gradient the place of the scaled weights holds the rows' arrival
+  // counters, which a scale of zero clears.  (No counter is kept in token_kl_out:
+  // a caller's buffer is only stored to and read, so it needs neither the
+  // alignment nor the memory that an atomic does.)
+  const float scale = grad_out ? grad_scale : 0.0f;
+  if (launch_prologue(sp, ws, L.nblk, alpha, scale, tiling.n_chunks, kl, stream) != hipSuccess)
     return TURNKL_ERR_HIP;
 
   RowParams rp{};

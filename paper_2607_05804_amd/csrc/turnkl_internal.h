@@ -280,7 +280,8 @@ struct RowParams {
   const void* zt;
   void* grad;
   const unsigned char* mask;
-  const float* wsc;
+  float* wsc;    // with a gradient: scaled weights; without: per row, as an
+                 // unsigned, the chunks that have published, zero before the kernel
   float* kl;
   Header* hdr;
   unsigned long long* slots;

@@ -88,3 +88,25 @@ def test_waves_in_both_forms(V, dtype, gpu):
         if r % 3 != 0:
             zt[r, k] += 340.0
     _forward(zs, zt, dtype, 0, 0, V)
+
+
+@pytest.mark.parametrize("n", [40, 8200])
+def test_a_workspace_after_a_call_with_a_gradient(n, gpu):
+    """The rows' arrival counters start from zero whatever the last call left in
+    the workspace (there: scaled weights), on both kinds of prologue."""
+    log(f"forward after a gradient call n={n}")
+    V = 51208  # two chunks
+    g = torch.Generator(device="cuda").manual_seed(n)
+    zs = torch.randn((n, V), generator=g, device="cuda").mul_(3).bfloat16()
+    zt = torch.randn((n, V), generator=g, device="cuda").mul_(3).bfloat16()
+    at = np.arange(n)
+    ids = ids_to_device((at // 12).astype(np.int32), (at // 3 % 4).astype(np.int32),
+                        (at % 5 != 0).astype(np.uint8))
+    want = T.fwd_bwd(zs, zt, *ids, 0.4, grad=None, max_turns=4, token_kl=True)
+    ws = T.Workspace(n, V, T.BF16, 4, aligned_rows=True)
+    T.fwd_bwd(zs, zt, *ids, 0.4, grad="new", grad_scale=-2.5, max_turns=4, workspace=ws)
+    for scale in (1.0, -3.0):
+        loss, _, _, kl, _ = T.fwd_bwd(zs, zt, *ids, 0.4, grad=None, grad_scale=scale, max_turns=4,
+                                      token_kl=True, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(loss, want[0]) and torch.equal(kl, want[3])
