@@ -351,10 +351,10 @@ constexpr int kOneSegs = 4096;   // 144 KiB of LDS
 constexpr int kOneTurns = 2048;  // turn indices under a support floor
 
 // One entry per segment; the trajectory sums are at its first segment.  In LDS
-// the weights take the place of start and traj, which are copied out by then.
+// the weights (their bits: one type per array) take the place of start and traj,
+// which are copied out by then.
 struct SegTable {
-  int *start, *end, *traj, *turn, *nsup, *head, *T, *N, *Tv;
-  float *w, *wsc;
+  int *start, *end, *traj, *turn, *nsup, *head, *T, *N, *Tv, *w, *wsc;
 };
 
 // A thread's tokens r * kOneThreads + threadIdx.x, r < rounds: their ids, and bit
@@ -528,8 +528,8 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
       w = (float)x;
       wsc = (float)(x * (double)grad_scale);
     }
-    t.w[s] = w;
-    t.wsc[s] = wsc;
+    t.w[s] = __float_as_int(w);
+    t.wsc[s] = __float_as_int(wsc);
   }
   if (err != kNoError) return;
   __syncthreads();
@@ -538,8 +538,8 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
     const int i = r * kOneThreads + tid;
     if (i >= (int)p.n) continue;
     const bool m = bit(own.sup, r);
-    ws.w[i] = m ? t.w[seg[r]] : 0.0f;
-    ws.wsc[i] = m ? t.wsc[seg[r]] : 0.0f;
+    ws.w[i] = m ? __int_as_float(t.w[seg[r]]) : 0.0f;
+    ws.wsc[i] = m ? __int_as_float(t.wsc[seg[r]]) : 0.0f;
   }
 }
 
@@ -613,12 +613,11 @@ __global__ __launch_bounds__(kOneThreads) void seg_one(SegParams p, Ws ws, doubl
   if (tid < rounds * kWaves) s_before[tid] = before;
   if (n_seg <= kOneSegs) {
     const SegTable tab{s_table[0], s_table[1], s_table[2], s_table[3], s_table[4], s_table[5],
-                       s_table[6], s_table[7], s_table[8], reinterpret_cast<float*>(s_table[0]),
-                       reinterpret_cast<float*>(s_table[2])};
+                       s_table[6], s_table[7], s_table[8], s_table[0], s_table[2]};
     one_table<true, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
   } else {
     // the weights' place: the segment moments, which are written later
-    float* const w = reinterpret_cast<float*>(ws.seg_stat);
+    int* const w = reinterpret_cast<int*>(ws.seg_stat);
     const SegTable tab{ws.seg_start, ws.tok_seg, ws.seg_traj, ws.seg_turn, ws.seg_nsup, ws.seg_head,
                        ws.traj_T, ws.traj_N, ws.traj_Tv, w, w + n};
     one_table<false, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
