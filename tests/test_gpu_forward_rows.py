@@ -12,7 +12,7 @@ from paper_2607_05804_amd import turnkl as T
 pytestmark = pytest.mark.gpu
 
 
-def _forward(zs, zt, dtype, vpt, ld=0, seed=0):
+def _forward(zs, zt, dtype, vpt, ld=0, seed=0, start=0, ld_t=None, start_t=None):
     n, V = zs.shape
     rng = np.random.default_rng(seed)
     traj = (np.arange(n) // 12).astype(np.int32)
@@ -26,14 +26,15 @@ def _forward(zs, zt, dtype, vpt, ld=0, seed=0):
                     O.DTYPE_BF16 if dtype == "bf16" else O.DTYPE_F32)
     turn_d, traj_d, mask_d = ids_to_device(traj, turn, mask)
 
-    def place(x):
+    def place(x, ld, start):
         if not ld:
             return x.cuda()
-        buf = torch.full((n, ld), 7.0, dtype=dt, device="cuda")
-        buf[:, :V] = x.cuda()
-        return buf[:, :V]
+        buf = torch.full((start + n * ld,), 7.0, dtype=dt, device="cuda")[start:].view(n, ld)[:, :V]
+        buf.copy_(x)
+        return buf
 
-    a, b = place(xs), place(xt)
+    a = place(xs, ld, start)
+    b = place(xt, ld if ld_t is None else ld_t, start if start_t is None else start_t)
     stats = T.new_turn_stats(4)
     lse = torch.empty((n, 2), dtype=torch.float32, device="cuda")
     T.set_row_tiling(vpt)
@@ -70,6 +71,21 @@ def test_forward(V, dtype, vpt, ld, shift, gpu):
     zs = rng.normal(0, 3, (25, V)) + shift
     zt = zs + rng.normal(0, 1, zs.shape) - 0.5 * shift
     _forward(zs, zt, dtype, vpt, ld, V)
+
+
+@pytest.mark.parametrize("V,dtype,ld,start,ld_t,start_t", [
+    (50257, "bf16", 50257, 0, 50304, 0), (50257, "bf16", 50300, 3, 50257, 11),
+    (50257, "f32", 50259, 5, 50304, 2),
+    (50176, "bf16", 50176, 0, 50180, 0),    # whole packs in one matrix only
+    (50176, "f32", 50176, 0, 50176, 1),
+    (16385, "bf16", 16400, 63, 16385, 1),
+])
+def test_matrices_at_their_own_starts_and_strides(V, dtype, ld, start, ld_t, start_t, gpu):
+    log(f"forward V={V} {dtype} ld={ld}+{start} teacher {ld_t}+{start_t}")
+    rng = np.random.default_rng(V + ld)
+    zs = rng.normal(0, 3, (25, V))
+    zs[5:8] += 500.0
+    _forward(zs, zs + rng.normal(0, 1, zs.shape), dtype, 0, ld, V, start, ld_t, start_t)
 
 
 @pytest.mark.parametrize("V,dtype", [(50176, "bf16"), (50257, "bf16"), (20001, "f32"), (120000, "f32")])

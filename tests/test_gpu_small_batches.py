@@ -14,11 +14,13 @@ pytestmark = pytest.mark.gpu
 
 V = 8
 TURNS = 1024
+LDS_SEGMENTS = 4096  # segments of a table in LDS
 
 
-def _batch(n, mean_len, seed):
+def _batch(n, mean_len, seed, segments=None):
     """n tokens in turns of about mean_len tokens, up to 40 turns a trajectory,
-    with padding between and inside trajectories' turns."""
+    with padding between and inside trajectories' turns (and after the first
+    `segments` segments)."""
     rng = np.random.default_rng(seed)
     traj, turn = np.full(n, -1, np.int32), np.zeros(n, np.int32)
     i, b, t = 0, 0, 0
@@ -31,22 +33,27 @@ def _batch(n, mean_len, seed):
         t += int(rng.integers(1, 3))
         if t >= 40 or rng.random() < 0.05:
             b, t = b + int(rng.integers(1, 4)), 0
+    if segments is not None:
+        start = (traj >= 0) & ((traj != np.roll(traj, 1)) | (turn != np.roll(turn, 1)))
+        traj[np.cumsum(start) > segments] = -1
     mask = ((traj >= 0) & (rng.random(n) < 0.6)).astype(np.uint8)
     mask[traj == 3] = 0
     zs = rng.normal(0.0, 3.0, (n, V)).astype(np.float32)
     return traj, turn, mask, zs, (zs + rng.normal(0.0, 1.0, zs.shape)).astype(np.float32)
 
 
-@pytest.mark.parametrize("n,mean_len", [
-    (1, 1), (63, 4), (1023, 30), (1024, 30), (1025, 30), (1025, 1),
-    (4096, 20), (4097, 20), (3000, 2),
-    (4096, 1), (8000, 3),                       # more than 2,048 segments
-    (8191, 40), (8192, 12), (8193, 12),         # the last goes to the tiled kernels
+@pytest.mark.parametrize("n,mean_len,segments", [
+    (1, 1, None), (63, 4, None), (1023, 30, None), (1024, 30, None), (1025, 30, None), (1025, 1, None),
+    (4096, 20, None), (4097, 20, None), (3000, 2, None),
+    (4096, 1, None), (8000, 3, None),                        # more than 2,048 segments
+    (6000, 1, 4095), (6000, 1, 4096),                        # the largest tables in LDS
+    (6000, 1, 4097), (6000, 1, 5000), (8000, 1, None), (8192, 1, None),  # tables beyond LDS
+    (8191, 40, None), (8192, 12, None), (8193, 12, None),    # the last goes to the tiled kernels
 ])
 @pytest.mark.parametrize("floor,frac", [(0, 0.0), (2, 0.15)])
-def test_segments_and_weights(n, mean_len, floor, frac, gpu):
-    log(f"small batch n={n} mean_len={mean_len} floor={floor}")
-    traj, turn, mask, zs, zt = _batch(n, mean_len, n + mean_len)
+def test_segments_and_weights(n, mean_len, segments, floor, frac, gpu):
+    log(f"small batch n={n} mean_len={mean_len} segments={segments} floor={floor}")
+    traj, turn, mask, zs, zt = _batch(n, mean_len, n + mean_len, segments)
     turn_d, traj_d, mask_d = ids_to_device(traj, turn, mask)
     success = (traj % 2 == 0).astype(np.uint8)
     stats, ostats = T.new_turn_stats(TURNS), T.new_turn_stats(2 * TURNS)
@@ -60,6 +67,10 @@ def test_segments_and_weights(n, mean_len, floor, frac, gpu):
     ref = O.fwd_bwd(traj, turn, mask, 0.3, TURNS, lambda r: (zs[r], zt[r]), O.DTYPE_F32,
                     support_floor=floor, support_frac=frac, success=success)
     assert ref.status == O.OK
+    if segments is not None:
+        assert ref.seg.count == segments
+    elif n >= 8000 and mean_len == 1:
+        assert ref.seg.count > LDS_SEGMENTS
     check_segments(ws, ref.seg)
     check_token_weights(w, ref.w, mask)
     check_loss(loss, ref.loss)
@@ -68,7 +79,7 @@ def test_segments_and_weights(n, mean_len, floor, frac, gpu):
     assert bool((kl[torch.from_numpy(mask).cuda() == 0] == 0).all())
 
 
-@pytest.mark.parametrize("n,mean_len", [(1500, 20), (3000, 1), (7000, 30), (8193, 30)])
+@pytest.mark.parametrize("n,mean_len", [(1500, 20), (3000, 1), (8000, 1), (7000, 30), (8193, 30)])
 @pytest.mark.parametrize("kind", ["pad_mask", "turn_high", "order", "outcome"])
 def test_the_earliest_error_is_reported(n, mean_len, kind, gpu):
     log(f"small batch error n={n} mean_len={mean_len} {kind}")

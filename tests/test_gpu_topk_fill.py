@@ -20,7 +20,8 @@ GUARD = 200
     (1, 777, 31, 5, "bf16"),     # one row
     (3, 5, 0, 1, "bf16"),        # fewer than two packs in all
     (21, 2048, 9, 0, "bf16"),    # rows at a stride, whole packs, off their lines
-    (21, 2049, 62, 1, "bf16"),   # one element past eight workgroups' packs
+    (21, 2049, 62, 1, "bf16"),   # one element past a workgroup's packs
+    (21, 16385, 62, 1, "bf16"),  # and past eight workgroups'
     (40, 8, 3, 0, "bf16"),       # one pack a row
     (300, 7, 4, 1, "bf16"),      # rows shorter than a pack
     (21, 1001, 0, 1, "f32"),
