@@ -334,27 +334,34 @@ __global__ __launch_bounds__(kSegThreads) void token_weights(SegParams p, Ws ws,
 }
 
 // ---------------------------------------------------------------------------
-// Batches of at most kOneTokens tokens: all of the above in one kernel.  One
-// workgroup holds the whole table (in LDS up to kOneSegs segments, beyond in
-// the workspace), the others clear the exchange slots and the per-token KL.
-// The four or five kernels above take 5 to 8 us each, nearly all of it launch
-// and memory latency; this one replaces them up to 8,192 tokens: 160 tokens of
-// 1,024 fp32 logits, whole call 35.9 -> 24.9 us; 4,096 tokens of the top-K call
-// 47 -> 33; 8,192 tokens 50 -> 40 (and 154 -> 142 with 1,024 bf16 logits).  At
-// 16,384 tokens one workgroup no longer beats the tiled kernels (56.5 against
-// 55.9 us).  A table beyond LDS costs its latency again: 8,192 tokens in 4,160
-// segments take 168 us either way.
+// Batches of at most kOneThreads * kOneMax tokens: all of the above in one
+// kernel.  One workgroup holds the whole table in LDS (as many segments as
+// tokens, 18 bytes each), the others clear the exchange slots and the per-token
+// KL.  The four or five kernels above take 5 to 8 us each, nearly all of it
+// launch and memory latency; this one takes 8 to 12, and 26 to 32 for the
+// largest tables.  Whole calls, tiled kernels -> this one: 160 tokens of 1,024
+// fp32 logits 35.8 -> 23.1 us; top-K with turns of 41 to 100 tokens, 1,000
+// tokens 35.6 -> 24.2, 8,192 tokens 42.6 -> 32.6; 8,192 turns of one token, as
+// many trajectories 169 -> 75 (1,024 bf16 logits), 205 trajectories 79 -> 84,
+// the one layout found that loses.  At 16,384 tokens one workgroup no longer
+// beats the tiled kernels (56.5 against 55.9 us).
 
 constexpr int kOneThreads = 1024;
-constexpr int kOneMax = 8;  // tokens per thread
-constexpr int kOneSegs = 4096;   // 144 KiB of LDS
+constexpr int kOneMax = 8;       // tokens per thread: 144 KiB of LDS
 constexpr int kOneTurns = 2048;  // turn indices under a support floor
 
-// One entry per segment; the trajectory sums are at its first segment.  In LDS
-// the weights (their bits: one type per array) take the place of start and traj,
-// which are copied out by then.
+// One entry per segment; the trajectory sums are at its first segment.  Token
+// indices, lengths and counts are at most 8,192: 16 bits each.  The weights (as
+// bits) take the place of traj and turn, which are copied out by then.
+template <int kMax>
 struct SegTable {
-  int *start, *end, *traj, *turn, *nsup, *head, *T, *N, *Tv, *w, *wsc;
+  static constexpr int kSegs = kOneThreads * kMax;
+  int traj[kSegs], turn[kSegs];
+  unsigned sums[kSegs];       // T_b << 16 | N_b; under a floor then T_vb << 16 | N_b
+  unsigned nsup2[kSegs / 2];  // supervised tokens, two segments to a word
+  unsigned short start[kSegs], head[kSegs];
+
+  __device__ int nsup(int s) const { return (nsup2[s >> 1] >> (16 * (s & 1))) & 0xFFFFu; }
 };
 
 // A thread's tokens r * kOneThreads + threadIdx.x, r < rounds: their ids, and bit
@@ -367,17 +374,17 @@ struct OwnTokens {
 };
 
 // an add that only this workgroup needs to see before the kernel ends
-__device__ inline void add_here(int* x, int n) {
+template <typename T>
+__device__ inline void add_here(T* x, T n) {
   __hip_atomic_fetch_add(x, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ inline bool bit(unsigned m, int j) { return (m >> j) & 1u; }
 
 // Everything after the segment count.  before[r * waves + w]: segments that
-// start before the tokens of wave w in round r.  kLds: the table is in LDS,
-// otherwise in the workspace.
-template <bool kLds, int kMax>
-__device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, const SegTable& t, int* s_surv,
+// start before the tokens of wave w in round r.
+template <int kMax>
+__device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, SegTable<kMax>& t, int* s_surv,
                                           const int* before, int n_seg, const OwnTokens<kMax>& own, int rounds,
                                           unsigned long long err, double alpha, float grad_scale) {
   constexpr int kWaves = kOneThreads / kWave;
@@ -386,10 +393,8 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   for (int s = tid; s < n_seg; s += kOneThreads) {
-    t.nsup[s] = 0;
-    t.T[s] = 0;
-    t.N[s] = 0;
-    t.Tv[s] = 0;
+    t.sums[s] = 0u;
+    t.nsup2[s >> 1] = 0u;
   }
   if (p.floor_on)
     for (int k = tid; k < p.max_turns; k += kOneThreads) s_surv[k] = 0;
@@ -406,63 +411,52 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
     const unsigned long long upto = ~0ull >> (kWave - 1 - lane);  // lanes 0 .. lane
     seg[r] = before[r * kWaves + tid / kWave] + __popcll(starts & upto) - 1;
     if (start) {
-      t.start[seg[r]] = i;
+      t.start[seg[r]] = (unsigned short)i;
       t.traj[seg[r]] = own.traj[r];
       t.turn[seg[r]] = own.turn[r];
     }
-    if (bit(own.last, r)) t.end[seg[r]] = i + 1;
+    if (bit(own.last, r)) t.head[seg[r]] = (unsigned short)i;  // the last token, for the length below
     // the first lane of each run of one segment adds the run's supervised tokens
     const unsigned long long after = cuts & ~upto;
     const unsigned long long run = (after ? (after & -after) - 1ull : ~0ull) & ~(upto >> 1);
-    const int n = __popcll(sup & run);
-    if (!pad && (start || lane == 0) && n) add_here(&t.nsup[seg[r]], n);
+    const unsigned n = (unsigned)__popcll(sup & run);
+    if (!pad && (start || lane == 0) && n) add_here(&t.nsup2[seg[r] >> 1], n << (16 * (seg[r] & 1)));
   }
   __syncthreads();
   int n_sup = 0;
-  // every lane of a wave runs the same iterations (the sums by head are wave-wide)
-  for (int s0 = 0; s0 < n_seg; s0 += kOneThreads) {
-    const int s = s0 + tid;
-    int n = 0, lo = 0;
-    if (s < n_seg) {
-      const int b = t.traj[s];
-      const int turn = t.turn[s];
-      if (s > 0) {
-        const int pb = t.traj[s - 1];
-        const int pt = t.turn[s - 1];
-        if (b < pb || (b == pb && turn <= pt)) {
-          const unsigned long long e = err_key(t.start[s], kPrioUnsorted);
-          err = e < err ? e : err;
-        }
-      }
-      int hi = s;  // first segment of this trajectory, as in seg_link
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (t.traj[mid] < b) lo = mid + 1; else hi = mid;
-      }
-      t.head[s] = lo;
-      if (p.success && lo != s && (p.success[t.start[s]] != 0) != (p.success[t.start[lo]] != 0)) {
-        const unsigned long long e = err_key(t.start[s], kPrioOutcome);
+  for (int s = tid; s < n_seg; s += kOneThreads) {
+    const int b = t.traj[s];
+    const int turn = t.turn[s];
+    const int start = t.start[s];
+    ws.seg_len[s] = t.head[s] + 1 - start;
+    if (s > 0) {
+      const int pb = t.traj[s - 1];
+      const int pt = t.turn[s - 1];
+      if (b < pb || (b == pb && turn <= pt)) {
+        const unsigned long long e = err_key(start, kPrioUnsorted);
         err = e < err ? e : err;
       }
-      n = t.nsup[s];
-      n_sup += n;
-      if (n > 0 && p.floor_on && turn >= 0 && turn < p.max_turns) add_here(&s_surv[turn], 1);
     }
-    if (kLds) {
-      if (n > 0) {
-        add_here(&t.T[lo], 1);
-        add_here(&t.N[lo], n);
-      }
-    } else {  // global atomics on one address take about 10 ns each
-      wave_by_head(lo, n, [&](int h, int n_turns, int sum_n) {
-        add_here(&t.T[h], n_turns);
-        add_here(&t.N[h], sum_n);
-      });
+    int lo = 0, hi = s;  // first segment of this trajectory, as in seg_link
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (t.traj[mid] < b) lo = mid + 1; else hi = mid;
+    }
+    t.head[s] = (unsigned short)lo;
+    if (p.success && lo != s && (p.success[start] != 0) != (p.success[t.start[lo]] != 0)) {
+      const unsigned long long e = err_key(start, kPrioOutcome);
+      err = e < err ? e : err;
+    }
+    const int n = t.nsup(s);
+    n_sup += n;
+    if (n > 0) {
+      add_here(&t.sums[lo], 0x10000u + (unsigned)n);
+      if (p.floor_on && turn >= 0 && turn < p.max_turns) add_here(&s_surv[turn], 1);
     }
   }
   __syncthreads();
   int b_eff = 0;
-  for (int s = tid; s < n_seg; s += kOneThreads) b_eff += t.N[s] > 0 ? 1 : 0;
+  for (int s = tid; s < n_seg; s += kOneThreads) b_eff += t.sums[s] ? 1 : 0;
   b_eff = wave_sum(b_eff);
   n_sup = wave_sum(n_sup);
   err = wave_min_u64(err);
@@ -491,45 +485,39 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
   const int n_min = p.floor_on ? support_n_min(p, b_eff) : 0;
   if (p.floor_on) {
     for (int k = tid; k < p.max_turns; k += kOneThreads) ws.turn_surv[k] = s_surv[k];
-    for (int s0 = 0; s0 < n_seg && err == kNoError; s0 += kOneThreads) {
-      const int s = s0 + tid;
-      const bool valid = s < n_seg && t.nsup[s] > 0 && s_surv[t.turn[s]] >= n_min;
-      const int head = valid ? t.head[s] : 0;
-      if (kLds) {
-        if (valid) add_here(&t.Tv[head], 1);
-      } else {
-        wave_by_head(head, valid ? 1 : 0, [&](int h, int n_turns, int) { add_here(&t.Tv[h], n_turns); });
-      }
+    for (int s = tid; s < n_seg; s += kOneThreads) {
+      ws.traj_T[s] = (int)(t.sums[s] >> 16);
+      t.sums[s] &= 0xFFFFu;
     }
     __syncthreads();
+    for (int s = tid; s < n_seg && err == kNoError; s += kOneThreads)
+      if (t.nsup(s) > 0 && s_surv[t.turn[s]] >= n_min) add_here(&t.sums[t.head[s]], 0x10000u);
+    __syncthreads();
   }
+  int* const turns = p.floor_on ? ws.traj_Tv : ws.traj_T;
   const double inv_b = b_eff > 0 ? 1.0 / (double)b_eff : 0.0;
   for (int s = tid; s < n_seg; s += kOneThreads) {
     const int h = t.head[s];
-    const int n = t.nsup[s];
-    const int start = t.start[s];
-    if (kLds) {
-      ws.seg_start[s] = start;
-      ws.seg_traj[s] = t.traj[s];
-      ws.seg_turn[s] = t.turn[s];
-      ws.seg_nsup[s] = n;
-      ws.seg_head[s] = h;
-      ws.traj_T[s] = t.T[s];
-      ws.traj_N[s] = t.N[s];
-      ws.traj_Tv[s] = t.Tv[s];
-    }
-    ws.seg_len[s] = t.end[s] - start;
+    const int n = t.nsup(s);
+    const unsigned own_sums = t.sums[s];
+    ws.seg_start[s] = t.start[s];
+    ws.seg_traj[s] = t.traj[s];
+    ws.seg_turn[s] = t.turn[s];
+    ws.seg_nsup[s] = n;
+    ws.seg_head[s] = h;
+    turns[s] = (int)(own_sums >> 16);
+    ws.traj_N[s] = (int)(own_sums & 0xFFFFu);
     float w = 0.0f, wsc = 0.0f;
     if (n > 0 && err == kNoError) {
-      const double n_b = (double)t.N[h];
-      TurnTerm u{(double)t.T[h], true};
-      if (p.floor_on) u = TurnTerm{(double)t.Tv[h], s_surv[t.turn[s]] >= n_min};
+      const unsigned sums = t.sums[h];
+      const double n_b = (double)(sums & 0xFFFFu);
+      const TurnTerm u{(double)(sums >> 16), !p.floor_on || s_surv[t.turn[s]] >= n_min};
       const double x = inv_b * ((1.0 - alpha) / n_b + turn_part(alpha, u, (double)n, n_b));
       w = (float)x;
       wsc = (float)(x * (double)grad_scale);
     }
-    t.w[s] = __float_as_int(w);
-    t.wsc[s] = __float_as_int(wsc);
+    t.traj[s] = __float_as_int(w);
+    t.turn[s] = __float_as_int(wsc);
   }
   if (err != kNoError) return;
   __syncthreads();
@@ -538,8 +526,8 @@ __device__ __forceinline__ void one_table(const SegParams& p, const Ws& ws, cons
     const int i = r * kOneThreads + tid;
     if (i >= (int)p.n) continue;
     const bool m = bit(own.sup, r);
-    ws.w[i] = m ? __int_as_float(t.w[seg[r]]) : 0.0f;
-    ws.wsc[i] = m ? __int_as_float(t.wsc[seg[r]]) : 0.0f;
+    ws.w[i] = m ? __int_as_float(t.traj[seg[r]]) : 0.0f;
+    ws.wsc[i] = m ? __int_as_float(t.turn[seg[r]]) : 0.0f;
   }
 }
 
@@ -555,7 +543,7 @@ __global__ __launch_bounds__(kOneThreads) void seg_one(SegParams p, Ws ws, doubl
     for (long long q = at; q < n; q += step) kl[q] = 0.0f;
     return;
   }
-  __shared__ int s_table[9][kOneSegs];
+  __shared__ SegTable<kMax> s_table;
   __shared__ int s_surv[kOneTurns];
   __shared__ int s_scan[kOneThreads / kWave];
   constexpr int kWaves = kOneThreads / kWave;
@@ -611,17 +599,7 @@ __global__ __launch_bounds__(kOneThreads) void seg_one(SegParams p, Ws ws, doubl
   const int k = tid < rounds * kWaves ? s_before[tid] : 0;
   const int before = block_exclusive_scan<kOneThreads>(k, s_scan, &n_seg);
   if (tid < rounds * kWaves) s_before[tid] = before;
-  if (n_seg <= kOneSegs) {
-    const SegTable tab{s_table[0], s_table[1], s_table[2], s_table[3], s_table[4], s_table[5],
-                       s_table[6], s_table[7], s_table[8], s_table[0], s_table[2]};
-    one_table<true, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
-  } else {
-    // the weights' place: the segment moments, which are written later
-    int* const w = reinterpret_cast<int*>(ws.seg_stat);
-    const SegTable tab{ws.seg_start, ws.tok_seg, ws.seg_traj, ws.seg_turn, ws.seg_nsup, ws.seg_head,
-                       ws.traj_T, ws.traj_N, ws.traj_Tv, w, w + n};
-    one_table<false, kMax>(p, ws, tab, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
-  }
+  one_table<kMax>(p, ws, s_table, s_surv, s_before, n_seg, own, rounds, err, alpha, grad_scale);
 }
 
 int grid_for(long long items, int per_block, int cap) {
