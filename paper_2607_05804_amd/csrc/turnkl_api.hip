@@ -137,11 +137,17 @@ RowTiling ragged_tiling(long long vocab, int dtype, uintptr_t start, long long s
 // 256 threads, 200 with 64).  Past kWholePacks the rows last longer than the
 // tickets, and workgroups that go on from row to row keep the stores in a
 // narrower window of addresses: 65,536 rows of 24,000 take 1,282 us here, 1,180
-// with tickets; of 16,384: 888, 918.
+// with tickets.  In large batches with a gradient that starts earlier
+// (whole packs only; ragged rows and calls without a gradient: not seen):
+// 65,536 rows of 16,384, all supervised, 1,140 and 1,081 us, 60% of them 912 and
+// 893; of 14,336: 1,009 and 991, but 787 and 873; 30,000 fp32 rows of 8,192, all
+// supervised: 542 and 518; 9,000 of 16,384: 179 and 192.
 // A ragged row needs every pack but a thread's first and last inside it, for
 // every start (see ragged_tiling).
 constexpr int kWavePacks = 512;
 constexpr int kWholePacks = 2048;
+constexpr int kLargeWholePacks = 1792;           // in batches of more than
+constexpr long long kLargeBatchPacks = 40000000;  // this many packs
 
 RowTiling whole_tiling(long long vocab, int dtype, bool ragged, uintptr_t start, long long stride) {
   RowTiling t{};
@@ -385,7 +391,8 @@ int fwd_bwd_impl(const void* student_logits, int64_t ld_student, const void* tea
     // the chunks that it asks for).
     if (vocab >= epv && (!ok || t_vpt_override == 0)) {
       const RowTiling w = whole_tiling(vocab, dtype, !ok, lines, stride);
-      if (w.threads) {
+      const bool tickets = ok && grad_out && w.packs > kLargeWholePacks && n_tokens * w.packs > kLargeBatchPacks;
+      if (w.threads && !tickets) {
         if (slot_chunks == 0) slot_chunks = tiling.n_chunks;
         tiling = w;
       }
