@@ -187,26 +187,47 @@ __global__ __launch_bounds__(kThreads) void topk_fill_flat(TopkParams p, long lo
     __builtin_nontemporal_store(z, reinterpret_cast<u32x4*>(g + head) + i);
 }
 
-// Rows at any stride and start, at least one pack long: one workgroup per
-// 256 packs of a row, on the grid of 128-byte lines; a pack that sticks out of
-// the row is moved inside it (its neighbour's elements are zeroed twice).
-template <bool kBf16>
-__global__ __launch_bounds__(kThreads) void topk_fill_rows(TopkParams p, unsigned per_row, long long blocks) {
+// Rows at any stride and start, at least one pack long: `per_row` packs each, on
+// the grid of the row's address & ~line; a pack that sticks out of the row is
+// moved inside it (its neighbour's elements are zeroed twice).  The workgroups
+// take the packs of all rows in order, so that short rows fill them too: 65,536
+// bf16 rows of 250 at a stride of 256 take 71 us a call, 90 with workgroups of
+// their own for every row.
+// kStream: nontemporal, as above; matrices that the last-level cache holds are
+// filled with default stores instead (see kCachedFill).
+typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+template <bool kBf16, bool kStream>
+__global__ __launch_bounds__(kThreads) void topk_fill_rows(TopkParams p, unsigned per_row, unsigned line,
+                                                           long long packs) {
   constexpr int kEs = kBf16 ? 2 : 4;
   constexpr int kEpv = 16 / kEs;
   if (!p.direct && p.hdr->err_key != kNoError) return;
-  const u32x4 z = {0u, 0u, 0u, 0u};
-  for (long long b = blockIdx.x; b < blocks; b += gridDim.x) {  // one turn up to kFillBlocks
-    const long long row = b / per_row;
-    char* const g = static_cast<char*>(p.grad) + row * p.ld_g * kEs;
-    const int pre = (int)(reinterpret_cast<uintptr_t>(g) & 127u) / kEs;
-    int e = (int)((unsigned)(b - row * per_row) * kThreads + threadIdx.x) * kEpv - pre;
+  const u32x4_any z = {0u, 0u, 0u, 0u};
+  for (long long i = (long long)blockIdx.x * kThreads; i < packs;
+       i += (long long)gridDim.x * kThreads) {  // one turn up to kFillBlocks
+    const long long row0 = i / per_row;
+    unsigned q = (unsigned)(i - row0 * per_row) + threadIdx.x;
+    const unsigned more = q / per_row;
+    q -= more * per_row;
+    if (row0 + more >= p.n_rows) continue;
+    char* const g = static_cast<char*>(p.grad) + (row0 + more) * p.ld_g * kEs;
+    const int pre = (int)((unsigned)reinterpret_cast<uintptr_t>(g) & line) / kEs;
+    int e = (int)q * kEpv - pre;
     if (e <= -kEpv || e >= p.vocab) continue;
     e = e < 0 ? 0 : (e > p.vocab - kEpv ? p.vocab - kEpv : e);
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g, 0, 0x7FFFFFFF, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b128(z, rsrc, e * kEs, 0, 2 /* nt */);
+    u32x4_any* const at = reinterpret_cast<u32x4_any*>(g + (long long)e * kEs);
+    if (kStream) __builtin_nontemporal_store(z, at);
+    else *at = z;
   }
 }
+
+// Bytes up to which rows at a stride are filled through the caches, out of place
+// and in place (where the rows' logits have just been read).  30,000 bf16 rows of
+// 3,000 at 3,001, 180 MB: 89 us a call, 99 nontemporal (in place 93, 114); 65,536
+// of 2,000, 262 MB: 139, 133 (141, 154); 65,536 of 3,000, 393 MB: 213, 171 (183,
+// 197); 65,536 fp32 rows of 2,000 at 2,003, 525 MB: 277, 176 (240, 203).
+constexpr double kCachedFill = 192.0 * (1 << 20);
+constexpr double kCachedFillInPlace = 384.0 * (1 << 20);
 
 // Rows shorter than a pack, with padding between them.
 template <bool kBf16>
@@ -276,11 +297,17 @@ void launch_fill(const TopkParams& p, hipStream_t s) {
     topk_fill_flat<kBf16><<<fill_grid((packs + kThreads - 1) / kThreads), kThreads, 0, s>>>(
         p, head, packs, elems);
   } else if (p.vocab >= kEpv) {
-    // the packs of a row that starts at the end of a line
-    const long long packs = (127 / kEs + (long long)p.vocab + kEpv - 1) / kEpv;
-    const unsigned per_row = (unsigned)((packs + kThreads - 1) / kThreads);
-    const long long blocks = (long long)p.n_rows * per_row;
-    topk_fill_rows<kBf16><<<fill_grid(blocks), kThreads, 0, s>>>(p, per_row, blocks);
+    // on the lines' grid (then also the packs of a row that starts at the end of
+    // one), unless its up to eight more packs weigh
+    const bool lines = p.vocab >= 64 * kEpv;
+    const unsigned per_row = (unsigned)(((lines ? 127 / kEs : 0) + (long long)p.vocab + kEpv - 1) / kEpv);
+    const long long packs = (long long)p.n_rows * per_row;
+    const dim3 grid = fill_grid((packs + kThreads - 1) / kThreads);
+    const unsigned line = lines ? 127u : 0u;
+    if ((double)elems * kEs <= (p.direct ? kCachedFill : kCachedFillInPlace))
+      topk_fill_rows<kBf16, false><<<grid, kThreads, 0, s>>>(p, per_row, line, packs);
+    else
+      topk_fill_rows<kBf16, true><<<grid, kThreads, 0, s>>>(p, per_row, line, packs);
   } else {
     topk_fill_short<kBf16><<<dim3((unsigned)((p.n_rows + kThreads - 1) / kThreads)), kThreads, 0, s>>>(p);
   }

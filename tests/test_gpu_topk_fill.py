@@ -22,6 +22,10 @@ GUARD = 200
     (21, 2048, 9, 0, "bf16"),    # rows at a stride, whole packs, off their lines
     (21, 2049, 62, 1, "bf16"),   # one element past a workgroup's packs
     (21, 16385, 62, 1, "bf16"),  # and past eight workgroups'
+    (300, 40, 3, 1, "bf16"),     # many rows to a workgroup
+    (200, 511, 2, 5, "bf16"),    # the longest rows on their own grid ...
+    (200, 512, 2, 5, "bf16"),    # ... and the shortest on the lines'
+    (1400, 151936, 1, 0, "bf16"),  # too large for default stores
     (40, 8, 3, 0, "bf16"),       # one pack a row
     (300, 7, 4, 1, "bf16"),      # rows shorter than a pack
     (21, 1001, 0, 1, "f32"),
