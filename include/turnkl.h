@@ -152,11 +152,12 @@ typedef struct {
  * and row strides in bytes are multiples of 16).  The size then covers the
  * 16-byte vector path, which every call with such rows takes when vocab
  * fills whole 16-byte vectors (vocab a multiple of 8 in bf16, of 4 in fp32).
- * aligned_rows = 0 covers whichever path a call takes.  The two differ in the
- * row kernel's exchange slots: at vocab = 151,936 in bf16, 96 bytes per token
- * on the vector path (3 chunks per row) and 608 on the element-wise path (19
- * chunks).  A call whose path needs more than the workspace it is given
- * returns TURNKL_ERR_WORKSPACE and enqueues nothing.
+ * aligned_rows = 0 covers rows of any start and length too, whose size is
+ * counted by chunks of 8,192 elements.  The two differ in the row kernel's
+ * exchange slots: at vocab = 151,936 in bf16, 96 bytes per token (3 chunks per
+ * row) and 608 (19 chunks; the kernel for such rows uses 128 of them).  A call
+ * that is given less workspace than its own rows' size returns
+ * TURNKL_ERR_WORKSPACE and enqueues nothing.
  *
  * Returns 0 when the arguments are invalid (n_tokens < 0, vocab < 1, unknown
  * dtype, max_turns < 1).  The workspace needs no initialisation; it must be

@@ -16,7 +16,7 @@
 // 128-byte) multiples from the row start when the host's tiling allows, else
 // balanced; each of a workgroup's 256 threads holds up to vpt packs.  One
 // workgroup owns one (row, chunk) task: it loads its chunk of both rows into
-// registers, reduces the chunk's partials, publishes them as seven tagged
+// registers, reduces the chunk's partials, publishes the seven of them as four
 // 64-bit words (see the row merge below), reads its row mates' words, merges
 // all chunks in chunk order (so every workgroup of the row computes
 // bit-identical row scalars), and writes its chunk of the gradient straight

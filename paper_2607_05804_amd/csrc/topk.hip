@@ -50,8 +50,9 @@ __device__ inline float wave_max_f(float v) { return wave_max(v); }
 // kPer support entries per lane (K <= 64 kPer), one row per wave.  The kernel is
 // bound by a chain of latencies, mask, ids, gathers and stores; many short waves
 // hide it better than fewer with several rows each, whose loads were issued
-// together (65,536 rows, K = 50, whole sparse call: 85 us with one row per wave,
-// 88 with two, 95 with four, 107 with eight; 4,000 rows: 26, 27, 30 and 37).
+// together (65,536 rows, K = 50, whole sparse call, one sweep: 85 us with one row
+// per wave, 88 with two, 95 with four, 107 with eight; 4,000 rows: 26, 27, 30 and
+// 37.  With the benchmark's batch and inputs the first takes 95 to 99).
 // The scaled gradient on the support goes to the stage (when there is one) and,
 // with p.direct, straight into a zero-filled, out-of-place dense gradient.
 template <int kPer>

@@ -311,9 +311,11 @@ hipError_t launch_whole_rows(const RowParams& p, const RowTiling& t, hipStream_t
 hipError_t launch_forward_rows(const RowParams& p, const RowTiling& t, hipStream_t s);
 
 // Top-K path (the teacher's top-K support; both distributions renormalised on
-// it).  The row kernel writes each supervised row's scaled gradient on the
-// support to `stage` (row stride ld_stage) and its KL; the dense kernel then
-// zero-fills every gradient row and scatters the staged values into it.
+// it).  topk_rows computes each supervised row's KL and its scaled gradient on
+// the support.  Out of place the dense gradient is zero-filled before, and
+// topk_rows writes the values into it; in place they go to `stage` (row stride
+// ld_stage), then the fill and a scatter follow.  A caller's sparse gradient is
+// the stage in both.
 struct TopkParams {
   const void* zs;
   const int* ids;
