@@ -34,10 +34,11 @@ int turnkl_profile_row_kernel(hipEvent_t before, hipEvent_t after);
  * n = vectors_per_thread is the most vectors a thread holds (1 to 25; default
  * 25).  Smaller n means more, smaller chunks per row, hence more exchange
  * slots: size the workspace with turnkl_testing_workspace_bytes for the same
- * n.  0 restores the default, under which rows of up to 2,048 vectors take one
- * workgroup each instead.  Rows that are no whole vectors, or do not start on
- * one, are tiled on their own and ignore the setting.  Results agree up to
- * floating-point summation order.  Returns TURNKL_ERR_INVALID_ARG for values outside 0..25.
+ * n.  0 restores the default, under which rows of up to 2,048 vectors (1,792 in
+ * large batches with a gradient) take one workgroup each instead.  Rows that
+ * are no whole vectors, or do not start on one, are tiled on their own and
+ * ignore the setting.  Results agree up to floating-point summation order.
+ * Returns TURNKL_ERR_INVALID_ARG for values outside 0..25.
  */
 int turnkl_set_row_tiling(int vectors_per_thread);
 

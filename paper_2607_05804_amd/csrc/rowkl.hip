@@ -33,8 +33,8 @@
 // HBM, at 5.5 TB/s for 6,000 bf16 rows of 50,257 elements (2.0 TB/s with one
 // element per load) and 5.85 TB/s for 3,000 fp32 rows.
 //
-// Rows of up to 2,048 packs take one workgroup each (kWhole, compiled in
-// rowkl_whole.hip), of one wave up to 512 packs, handed out by the hardware's
+// Rows of up to 2,048 packs (1,792 in large batches) take one workgroup each
+// (kWhole, compiled in rowkl_whole.hip), of one wave up to 512 packs, handed out by the hardware's
 // dispatch: their loads, sums and stores last less than the queue for the one
 // ticket counter.  What bounds them is latency below about 2,000 elements
 // (65,536 bf16 rows of 1,024: 94 us a call, 49 of them the other kernels), HBM

@@ -48,3 +48,33 @@ def test_rows_with_a_workgroup_each(V, dtype, n, shift, grad, gpu):
     if grad is not None:
         check_grad_rows(out, ref, 1.0, rows, mask)
         assert bool((out[torch.from_numpy(mask).cuda() == 0] == 0).all())
+
+
+@pytest.mark.parametrize("n,grad", [(19520, "new"), (19584, "new"), (19584, None)])
+def test_either_side_of_a_large_batch(n, grad, gpu):
+    """Rows of 2,048 packs: above 40 million packs (19,532 rows) with a gradient
+    they take tickets; one row in 97 supervised, the others zeros."""
+    log(f"large batch n={n} {grad}")
+    V = 16384
+    rng = np.random.default_rng(n)
+    sup = np.arange(0, n, 97)
+    traj, turn = (np.arange(n) // 2000).astype(np.int32), (np.arange(n) // 500 % 4).astype(np.int32)
+    mask = np.zeros(n, np.uint8)
+    mask[sup] = 1
+    zs = np.zeros((n, V), np.uint16)
+    zt = np.zeros((n, V), np.uint16)
+    a = rng.normal(0, 3, (sup.size, V)).astype(np.float32)
+    to_bits = lambda x: torch.from_numpy(x).bfloat16().view(torch.int16).numpy().view(np.uint16)
+    zs[sup], zt[sup] = to_bits(a), to_bits(a + rng.normal(0, 1, a.shape).astype(np.float32))
+    ref = O.fwd_bwd(traj, turn, mask, 0.4, 4, lambda r: (zs[r], zt[r]), O.DTYPE_BF16, 1.0, list(sup))
+    dev = lambda x: torch.from_numpy(x.view(np.int16)).cuda().view(torch.bfloat16)
+    out = torch.full((n, V), 9.0, dtype=torch.bfloat16, device="cuda") if grad else None
+    loss, out, _, kl, _ = T.fwd_bwd(dev(zs), dev(zt), *ids_to_device(traj, turn, mask), 0.4, grad=out,
+                                    max_turns=4, token_kl=True)
+    torch.cuda.synchronize()
+    check_loss(loss, ref.loss)
+    check_token_kl(kl, ref.kl, mask)
+    if grad:
+        check_grad_rows(out, ref, 1.0, list(sup), mask)
+        assert int(torch.count_nonzero(out).item()) == int(torch.count_nonzero(
+            out.index_select(0, torch.from_numpy(sup).cuda())).item())
